@@ -16,6 +16,7 @@
 #include <cstring>
 #include <string>
 
+#include "overlap.h"
 #include "runtime.h"
 #include "serve.h"
 
@@ -468,6 +469,12 @@ int sparkcl::build_plan(sparkcl_ctx *ctx, int kind, int mode, const sparkcl_task
     if (total_tiles > 0xFFFFFFF0ull)
         return fail(SPARKCL_ETOOBIG, "too many tiles in one call");
     p->ntiles_total = (uint32_t)total_tiles;
+    if (kind == 1) {
+        p->map_first.assign(ntasks + 1, 0);
+        for (uint32_t i = 0; i < ntasks; ++i)
+            p->map_first[i + 1] = p->map_first[i] + (tasks[i].n + kMapTile - 1) / kMapTile;
+        p->map_together = tasks_independent(tasks, ntasks);
+    }
 
     void *m = nullptr;
     int rc;
@@ -517,6 +524,8 @@ int sparkcl::build_plan(sparkcl_ctx *ctx, int kind, int mode, const sparkcl_task
         fill_taskdev(t, p->variants[i], tile[i], p->ntiles[i], i,
                      p->dparts ? p->dparts + first[i] : nullptr,
                      kernel_unroll(ctx->tuning, t.kernel_id), &d);
+        if (kind == 1)
+            d.tile_first = p->map_first[i];
         if (host_in) {
             char *base = p->staging + (uint64_t)(i % p->nslots) * p->slot_bytes;
             d.in0 = reinterpret_cast<const float *>(base + ((uintptr_t)t.in0 & 15u));
@@ -1045,16 +1054,20 @@ int sparkcl_map(sparkcl_ctx *ctx, const sparkcl_task *tasks, uint32_t ntasks, vo
     Plan *p = nullptr;
     if ((rc = get_plan(ctx, 1, 0, tasks, ntasks, nullptr, nullptr, s, &p)) != SPARKCL_OK)
         return rc;
-    const uint32_t cap = (uint32_t)ctx->occ_batch * (uint32_t)ctx->cus;
-    for (uint32_t i = 0; i < ntasks; ++i) {
-        const uint64_t n = tasks[i].n;
-        if (n == 0)
-            continue;
-        const uint64_t want = (n / 4 + kBlock - 1) / kBlock;
-        const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(want, cap));
-        if ((rc = launch_map(p->dtasks + i, n, p->variants[i], grid, s)) != SPARKCL_OK)
+    // One launch over the tiles of all tasks; tasks whose outputs overlap
+    // other tasks' arrays run one launch each, in task order.
+    const std::vector<uint64_t> &first = p->map_first;
+    if (p->map_together) {
+        if (first[ntasks] &&
+            (rc = launch_map(p->dtasks, ntasks, 0, first[ntasks], s)) != SPARKCL_OK)
             return fail(rc, "map launch failed");
+        return SPARKCL_OK;
     }
+    for (uint32_t i = 0; i < ntasks; ++i)
+        if (first[i + 1] != first[i] &&
+            (rc = launch_map(p->dtasks + i, 1, first[i], first[i + 1] - first[i], s)) !=
+                SPARKCL_OK)
+            return fail(rc, "map launch failed");
     return SPARKCL_OK;
 }
 

@@ -1,5 +1,5 @@
-// C shim over the pure host logic (arena allocator, serving admission control,
-// tuning table and its JSON cache) so it can be unit-tested on a machine
+// C shim over the pure host logic (arena allocator, map-call overlap check,
+// serving admission control, tuning table and its JSON cache) so it can be unit-tested on a machine
 // without a GPU.  Built with g++ into libsparkcl_host.so; it is not part of
 // the product library's ABI.
 #include <cstring>
@@ -8,6 +8,7 @@
 
 #include "admission.h"
 #include "arena.h"
+#include "overlap.h"
 #include "tuning.h"
 
 using namespace sparkcl;
@@ -39,6 +40,11 @@ uint64_t hl_arena_largest_free(void *a) { return static_cast<Arena *>(a)->larges
 uint64_t hl_arena_free_blocks(void *a) { return static_cast<Arena *>(a)->free_blocks(); }
 uint64_t hl_arena_live_blocks(void *a) { return static_cast<Arena *>(a)->live_blocks(); }
 uint64_t hl_arena_size(void *a) { return static_cast<Arena *>(a)->size(); }
+
+int hl_tasks_independent(const sparkcl_task *tasks, uint32_t ntasks)
+{
+    return tasks_independent(tasks, ntasks) ? 1 : 0;
+}
 
 void *hl_adm_new(uint64_t budget, uint32_t slots, uint64_t tile_cap)
 {

@@ -960,40 +960,92 @@ __global__ __launch_bounds__(kBlock) void k_chain(const TaskDev *__restrict__ ta
              [&](const TaskDev *tp, uint32_t j) { return chain_tile<UC>(tp, chain, j, L); });
 }
 
-// MapCL materialisation only (no reduction): out[i] = map(x[i] [, y[i]]),
-// grid-stride over float4 quads when the arrays share their alignment.
+// MapCL materialisation only (no reduction): out[i] = map(x[i] [, y[i]]) for
+// the tasks of a call, all in one launch.  Block b runs tile b: kMapUnroll
+// quads per thread, all loads issued before the first store, and ends; a
+// launch has one block per tile rather than a loop over few blocks.  The map
+// is bound by HBM (and below a few MB by the launch), and short blocks of
+// plain stores behind nontemporal loads keep both directions busiest
+// (measured on MI355X, x*y + c*x over 2^26 elements: 105.7 us, 7.6 TB/s;
+// nontemporal stores 123 us; one quad per thread in a loop over 768 blocks,
+// the earlier kernel, 129 us; 2^28 elements: 530 us against 557).  Calls:
+// 64 FMUL tasks of 2^20 elements 133 us (one launch per task: 230 us), 256
+// POLY tasks of 20001 elements 10.4 us (774 us).
 template <class M>
-__device__ __forceinline__ void map_only(const M &f, const float *__restrict__ x,
+__device__ __forceinline__ void map_tile(const M &f, const float *__restrict__ x,
                                          const float *__restrict__ y,
-                                         float *__restrict__ out, uint64_t n)
+                                         float *__restrict__ out, uint64_t n, uint64_t j)
 {
-    const uint64_t stride = (uint64_t)gridDim.x * kBlock;
-    const uint64_t gtid = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    const uint64_t head = quad_head(x, n);
-    for (uint64_t i = gtid; i < head; i += stride)
-        st1(out + i, f(ld1(x + i), M::kTwo ? ld1(y + i) : 0.0f));
+    constexpr int NY = M::kTwo ? kMapUnroll : 1;
+    const uint32_t tid = threadIdx.x;
+    const uint32_t head = quad_head(x, n);
     const uint64_t nq = (n - head) >> 2;
     const float *x4 = x + head;
     const float *y4 = M::kTwo ? y + head : nullptr;
     float *o4 = out + head;
-    for (uint64_t q = gtid; q < nq; q += stride) {
-        const float4 xv = ld4(x4 + 4 * q);
-        const float4 yv = M::kTwo ? ld4u(y4 + 4 * q) : xv;
+    auto quad = [&](uint64_t q, const float4 &xv, const float4 &yv) {
         float4 v;
         v.x = f(xv.x, yv.x);
         v.y = f(xv.y, yv.y);
         v.z = f(xv.z, yv.z);
         v.w = f(xv.w, yv.w);
-        st4u(o4 + 4 * q, v);
+        *(gf4uw *)(o4 + 4 * q) = f4a4{v.x, v.y, v.z, v.w};
+    };
+    const uint64_t q0 = j * (kMapUnroll * kBlock) + tid;
+    if ((j + 1) * (kMapUnroll * kBlock) <= nq) {
+        float4 xv[kMapUnroll], yv[NY];
+#pragma unroll
+        for (int u = 0; u < kMapUnroll; ++u) {
+            xv[u] = ld4(x4 + 4 * (q0 + u * kBlock));
+            if (M::kTwo)
+                yv[u] = ld4u(y4 + 4 * (q0 + u * kBlock));
+        }
+#pragma unroll
+        for (int u = 0; u < kMapUnroll; ++u)
+            quad(q0 + u * kBlock, xv[u], M::kTwo ? yv[u] : xv[u]);
+    } else {
+        for (uint64_t q = q0; q < nq; q += kBlock) {
+            const float4 xv = ld4(x4 + 4 * q);
+            quad(q, xv, M::kTwo ? ld4u(y4 + 4 * q) : xv);
+        }
     }
-    const uint64_t t0 = head + 4 * nq;
-    if (gtid < n - t0)
-        st1(out + t0 + gtid, f(ld1(x + t0 + gtid), M::kTwo ? ld1(y + t0 + gtid) : 0.0f));
+    if (j == 0) { // the unaligned head and the ragged tail: at most 3 each
+        const uint64_t t0 = head + 4 * nq;
+        if (tid < head)
+            st1(out + tid, f(ld1(x + tid), M::kTwo ? ld1(y + tid) : 0.0f));
+        if (tid < n - t0)
+            st1(out + t0 + tid, f(ld1(x + t0 + tid), M::kTwo ? ld1(y + t0 + tid) : 0.0f));
+    }
 }
 
-__global__ __launch_bounds__(kBlock) void k_map(const TaskDev *__restrict__ tp,
-                                                uint64_t n, uint32_t variant)
+// The task of tile t among `count` tasks whose first tiles ascend from
+// tasks[0].tile_first <= t: the last one with tile_first <= t (tasks without
+// tiles share the next one's, and so are passed over).  A wave reads 64
+// candidates at a time, so 4096 tasks take two rounds of loads.
+__device__ __forceinline__ uint32_t task_of_tile(const TaskDev *__restrict__ tasks,
+                                                 uint32_t count, uint64_t t)
 {
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t lo = 0;
+    while (count > 1) {
+        const uint32_t step = (count + 63) / 64;
+        const uint32_t at = lane * step;
+        const bool le = at < count && tasks[lo + at].tile_first <= t;
+        const uint32_t k = (uint32_t)__popcll(__ballot(le)) - 1u; // lane 0 always holds
+        lo += k * step;
+        count = min(step, count - k * step);
+    }
+    return uni(lo);
+}
+
+__global__ __launch_bounds__(kBlock) void k_map(const TaskDev *__restrict__ tasks,
+                                                uint32_t ntasks, uint64_t tile0)
+{
+    const uint64_t t = tile0 + blockIdx.x;
+    const TaskDev *tp = tasks + task_of_tile(tasks, ntasks, t);
+    const uint64_t j = t - uni64(tp->tile_first);
+    const uint64_t n = uni64(tp->n);
+    const uint32_t variant = uni(tp->variant);
     const float *x = tp->in0;
     const float *y = tp->in1;
     float *o = tp->out;
@@ -1006,7 +1058,7 @@ __global__ __launch_bounds__(kBlock) void k_map(const TaskDev *__restrict__ tp,
         PolyMap<D> f;                                                          \
         for (int i = 0; i < 8; ++i)                                            \
             f.k[i] = k[i];                                                     \
-        map_only(f, x, y, o, n);                                               \
+        map_tile(f, x, y, o, n, j);                                            \
     } break;
         switch (variant & 7u) {
             SPARKCL_MAP_CASE(0)
@@ -1021,7 +1073,7 @@ __global__ __launch_bounds__(kBlock) void k_map(const TaskDev *__restrict__ tp,
 #undef SPARKCL_MAP_CASE
     } else {
         FmulMap f{tp->c};
-        map_only(f, x, y, o, n);
+        map_tile(f, x, y, o, n, j);
     }
 }
 
@@ -2010,14 +2062,21 @@ int launch_batch(const TaskDev *dtasks, const TileRef *tiles, uint32_t ntiles,
     return hip_status(hipGetLastError());
 }
 
-int launch_map(const TaskDev *dtask, uint64_t n, uint32_t variant, uint32_t grid,
+int launch_map(const TaskDev *dtasks, uint32_t ntasks, uint64_t tile0, uint64_t ntiles,
                void *stream)
 {
-    if (grid == 0)
+    if (ntasks == 0 || ntiles == 0)
         return SPARKCL_EINVAL;
-    hipLaunchKernelGGL(k_map, dim3(grid), dim3(kBlock), 0, (hipStream_t)stream,
-                       dtask, n, variant);
-    return hip_status(hipGetLastError());
+    constexpr uint64_t kMost = 1ull << 30; // blocks per launch
+    for (uint64_t at = 0; at < ntiles; at += kMost) {
+        const uint32_t grid = (uint32_t)(ntiles - at < kMost ? ntiles - at : kMost);
+        hipLaunchKernelGGL(k_map, dim3(grid), dim3(kBlock), 0, (hipStream_t)stream, dtasks,
+                           ntasks, tile0 + at);
+        const int rc = hip_status(hipGetLastError());
+        if (rc != SPARKCL_OK)
+            return rc;
+    }
+    return SPARKCL_OK;
 }
 
 int launch_wordcount(const WcArgs &a, uint32_t grid, void *stream)

@@ -75,6 +75,10 @@ struct Plan {
     uint32_t ntiles_total = 0;
     std::vector<uint32_t> ntiles;
     std::vector<uint32_t> variants;
+    // kind 1, maps: the tasks' first tiles (and their number at the end), and
+    // whether the tasks are independent (run in one launch)
+    std::vector<uint64_t> map_first;
+    bool map_together = false;
     uint32_t grid = 0;
     uint32_t block = 256; // executor threads per block
     bool mc_only = false; // every task Monte-Carlo: the executor's MC instance

@@ -62,7 +62,7 @@ struct TaskDev {
     uint32_t index;      // result / sync slot of this task
     Partial *partials;   // ntiles entries
     uint64_t seq;        // serving sequence number (0 in batch launches)
-    uint64_t tile_first; // serving: global index of the task's first tile
+    uint64_t tile_first; // serving and maps: index of the task's first tile
 };
 static_assert(sizeof(TaskDev) == 128, "TaskDev layout");
 
@@ -144,8 +144,14 @@ int launch_task(const TaskDev *dtask, uint32_t ntiles, uint32_t grid,
 int launch_batch(const TaskDev *dtasks, const TileRef *tiles, uint32_t ntiles,
                  uint32_t grid, const LaunchOut &out, void *stream, uint32_t block = kBlock,
                  bool mc_only = false);
-int launch_map(const TaskDev *dtask, uint64_t n, uint32_t variant,
-               uint32_t grid, void *stream);
+// MapCL tiles: float4 quads per thread and array of one block.
+constexpr int kMapUnroll = 4;
+constexpr uint64_t kMapTile = 4ull * kMapUnroll * kBlock; // elements per block
+// Tiles [tile0, tile0 + ntiles) of a map call whose tasks dtasks[0..ntasks)
+// hold their first tiles in tile_first, ascending; task 0's is at most tile0
+// and the tasks' tiles reach tile0 + ntiles.
+int launch_map(const TaskDev *dtasks, uint32_t ntasks, uint64_t tile0, uint64_t ntiles,
+               void *stream);
 int launch_zero(void *p, uint64_t bytes, void *stream);
 // Map chains: up to kMaxPost POLY stages after a task's registry map.
 constexpr int kMaxPost = 4;
