@@ -69,10 +69,6 @@ int build_tree_plan(sparkcl_ctx *ctx, uint32_t combiner, const float *const *arr
     p->nleaves = k;
     p->leaf_base = base;
     p->leaf_stride = stride;
-    // float4 columns whenever the length is a multiple of 4: leaves and out
-    // need only their 4-byte alignment (a 16-byte access at a 4-byte-aligned
-    // address is one dwordx4 instruction)
-    const bool vec4 = (len & 3u) == 0;
     if (arrays) {
         p->leaves.assign(arrays, arrays + k);
         for (uint32_t i = 0; i < k; ++i) {
@@ -82,15 +78,45 @@ int build_tree_plan(sparkcl_ctx *ctx, uint32_t combiner, const float *const *arr
                 return fail(SPARKCL_EINVAL, "arrays must be 4-byte aligned");
         }
     }
-    p->vec4 = vec4;
-    const uint64_t V = vec4 ? 4 : 1;
-    const uint64_t colblocks = (len + kBlock * V - 1) / (kBlock * V);
+    // float4 columns for every length of at least 4 (the last one may overlap
+    // the one before): leaves and out need only their 4-byte alignment (a
+    // 16-byte access at a 4-byte-aligned address is one dwordx4 instruction).
+    // 48 arrays of 1000003 floats took 39.7 us in single columns.
+    const uint64_t ncol = len < 4 ? len : (len + 3) / 4;
+    const uint64_t colblocks = (ncol + kBlock - 1) / kBlock;
     const uint64_t target = 4ull * (uint64_t)ctx->cus; // blocks that fill the GPU
 
     std::vector<uint32_t> rows; // output rows of each pass
     uint32_t count = k;
     for (;;) {
-        uint32_t chunk = 0, cpt = 1, threads = kBlock;
+        uint32_t chunk = 0, cpt = 1, threads = kBlock, groups = 0, cols = 0;
+        // Short arrays: as many groups of threads as a block holds, each
+        // folding leaves of its own.  Rows past 1 KiB (64 quads) are cut
+        // into column tiles of about that while the input fits the
+        // memory-side cache, which spreads a pass over more blocks (8000
+        // rows of 1024 floats: 12 us, whole rows 17; 65536 rows of 1000: 50
+        // and 56); past it whole rows stream better (131072 rows of 2047:
+        // 217 us, tiles 237).  A pass that one block per tile can read as
+        // 128 KiB at most is the last; one before it takes 8 to 64 leaves per
+        // thread, as many as still leave two blocks per CU (2^20 rows of 64:
+        // 49 us, with four blocks 57).
+        if (ncol <= kTreeFlatThreads) {
+            const uint64_t most =
+                (uint64_t)count * len * 4 <= kTreeCached ? 64 : kTreeFlatThreads;
+            const uint64_t tiles = (ncol + most - 1) / most;
+            cols = (uint32_t)((ncol + tiles - 1) / tiles);
+            groups = pow2_floor(kTreeFlatThreads / cols);
+            threads = (cols * groups + 63) / 64 * 64;
+            uint32_t per;
+            if ((uint64_t)count * cols * 16 <= (128u << 10)) {
+                per = pow2_floor(2ull * ((count + groups - 1) / groups) - 1);
+            } else {
+                const uint64_t fill = 2ull * (uint64_t)ctx->cus * groups;
+                per = pow2_floor(std::max<uint64_t>(1, count * tiles / fill));
+                per = std::min(std::max(per, 8u), kTreeFlatPer);
+            }
+            chunk = per * groups;
+        }
         // float4 columns: the wide kernel (leaf pairs, 2 or 4 columns per
         // thread, chunks of up to 64 leaves) when its grid still fills half
         // the GPU's block slots and at most one more pass follows (many
@@ -100,10 +126,10 @@ int build_tree_plan(sparkcl_ctx *ctx, uint32_t combiner, const float *const *arr
         // thread first, in blocks of kTreeWideBig threads when those alone
         // give every CU two blocks (64 arrays of 2^22 floats: 163 us against
         // 170 us in 256-thread blocks)
-        if (vec4) {
+        if (groups == 0) {
             const uint32_t ch = std::min<uint32_t>(count, kTreeWideChunk);
             const uint64_t nch = (count + (uint64_t)ch - 1) / ch;
-            const uint64_t cb_big = (len / 4 + kTreeWideBig * 4ull - 1) / (kTreeWideBig * 4ull);
+            const uint64_t cb_big = (ncol + kTreeWideBig * 4ull - 1) / (kTreeWideBig * 4ull);
             if (nch <= kTreeWideChunk && cb_big * nch >= 2ull * (uint64_t)ctx->cus) {
                 cpt = 4;
                 threads = kTreeWideBig;
@@ -112,7 +138,7 @@ int build_tree_plan(sparkcl_ctx *ctx, uint32_t combiner, const float *const *arr
             for (uint32_t c : {4u, 2u}) {
                 if (cpt > 1)
                     break;
-                const uint64_t cb = (len / 4 + (uint64_t)kBlock * c - 1) / ((uint64_t)kBlock * c);
+                const uint64_t cb = (ncol + (uint64_t)kBlock * c - 1) / ((uint64_t)kBlock * c);
                 if (nch <= kTreeWideChunk && cb * nch >= target / 2) {
                     cpt = c;
                     chunk = ch;
@@ -123,7 +149,7 @@ int build_tree_plan(sparkcl_ctx *ctx, uint32_t combiner, const float *const *arr
         // One pass when the columns alone fill the GPU (then long per-thread
         // chains are hidden by other waves) or the chain is short; else fold
         // chunks so the grid of columns x chunks fills the GPU.
-        if (cpt > 1) {
+        if (cpt > 1 || groups != 0) {
             // chosen above
         } else if (count <= kTreeMaxChunk && (colblocks >= target || count <= 64)) {
             chunk = count; // final pass
@@ -143,6 +169,8 @@ int build_tree_plan(sparkcl_ctx *ctx, uint32_t combiner, const float *const *arr
         a.chunk = chunk;
         a.cpt = cpt;
         a.threads = threads;
+        a.groups = groups;
+        a.cols = cols;
         p->passes.push_back(a);
         rows.push_back(nchunks);
         if (nchunks == 1)
@@ -251,7 +279,7 @@ int reduce_tree(sparkcl_ctx *ctx, uint32_t combiner, const float *const *arrays,
         ctx->plans.push_front(p);
     }
     for (const TreeArgs &a : p->passes)
-        if ((rc = launch_tree(a, combiner, p->vec4, s)) != SPARKCL_OK)
+        if ((rc = launch_tree(a, combiner, s)) != SPARKCL_OK)
             return fail(rc, "array reduce launch failed");
     return SPARKCL_OK;
 }

@@ -1153,17 +1153,42 @@ __global__ __launch_bounds__(kBlock) void k_map(const TaskDev *__restrict__ task
 // rebuilds the tree over all elements.
 constexpr int kTreeSlots = 13; // up to 2^12 leaves per chunk
 
+// Float4 columns cover any length of at least 4: the last quad of a length
+// that is no multiple of 4 is moved back to end at the array's end, and its
+// thread stores only the columns that the quad before does not own (so a
+// column is stored by one thread, and read before by no other that keeps it).
 template <int V> struct TreeVec;
 template <> struct TreeVec<1> {
     typedef float T;
     static __device__ __forceinline__ T ld(const float *p) { return ld1(p); }
-    static __device__ __forceinline__ void st(float *p, T v) { st1(p, v); }
+    static __device__ __forceinline__ void st(float *p, T v, uint32_t) { st1(p, v); }
 };
 template <> struct TreeVec<4> {
     typedef float4 T;
     static __device__ __forceinline__ T ld(const float *p) { return ld4u(p); }
-    static __device__ __forceinline__ void st(float *p, T v) { st4u(p, v); }
+    // columns skip..3 of the quad at p
+    static __device__ __forceinline__ void st(float *p, const T &v, uint32_t skip)
+    {
+        if (skip == 0) {
+            st4u(p, v);
+            return;
+        }
+        if (skip <= 1)
+            st1(p + 1, v.y);
+        if (skip <= 2)
+            st1(p + 2, v.z);
+        st1(p + 3, v.w);
+    }
 };
+// First column of vector column q of arrays of len floats (len >= V), and how
+// many of its columns belong to the vector before.
+template <int V>
+__device__ __forceinline__ uint64_t tree_col(uint64_t q, uint64_t len, uint32_t &skip)
+{
+    const uint64_t at = min(q * V, len - V);
+    skip = (uint32_t)(q * V - at);
+    return at;
+}
 
 template <uint32_t COMB>
 __device__ __forceinline__ float comb1(float a, float b)
@@ -1187,13 +1212,13 @@ __device__ __forceinline__ float4 comb(const float4 &a, const float4 &b)
 // Insert a perfect subtree of 2^L leaves that starts at leaf `pos` (a
 // multiple of 2^L) into the counter.  `pos` is wave-uniform, so every branch
 // here is a scalar branch and every slot index is a compile-time constant.
-template <int L, uint32_t COMB, class T>
-__device__ __forceinline__ void tree_insert(T (&slot)[kTreeSlots], uint32_t pos, T v)
+template <int L, uint32_t COMB, class T, int N>
+__device__ __forceinline__ void tree_insert(T (&slot)[N], uint32_t pos, T v)
 {
     // the carry chain: the full slots L, L+1, ... below the first empty one
     const uint32_t full = (uint32_t)__builtin_ctz(~(pos >> L));
 #pragma unroll
-    for (int j = L; j < kTreeSlots; ++j) {
+    for (int j = L; j < N; ++j) {
         if ((uint32_t)j < L + full)
             v = comb<COMB>(slot[j], v);
         else if ((uint32_t)j == L + full)
@@ -1201,45 +1226,113 @@ __device__ __forceinline__ void tree_insert(T (&slot)[kTreeSlots], uint32_t pos,
     }
 }
 
-template <int V, uint32_t COMB>
-__global__ __launch_bounds__(kBlock) void k_tree(TreeArgs a)
+// The tree over leaves [0, m) of one vector column, each read with leaf(i).
+template <uint32_t COMB, int N, class T, class Leaf>
+__device__ __forceinline__ T tree_fold(uint32_t m, Leaf leaf)
 {
-    typedef TreeVec<V> TV;
-    typedef typename TV::T T;
-    const uint64_t col = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) * V;
-    if (col >= a.len)
-        return; // no barriers below
-    const uint32_t c = blockIdx.y;
-    const uint32_t k0 = c * a.chunk;
-    const uint32_t m = min(a.count - k0, a.chunk);
-    auto leaf = [&](uint32_t i) -> const float * {
-        const uint32_t kk = k0 + i;
-        return (a.ptrs ? a.ptrs[kk] : a.base + (uint64_t)kk * a.stride) + col;
-    };
-    T slot[kTreeSlots];
+    T slot[N];
     uint32_t i = 0;
     for (; i + 8 <= m; i += 8) {
         T v[8];
 #pragma unroll
         for (int b = 0; b < 8; ++b)
-            v[b] = TV::ld(leaf(i + b));
+            v[b] = leaf(i + b);
         const T l = comb<COMB>(comb<COMB>(v[0], v[1]), comb<COMB>(v[2], v[3]));
         const T r = comb<COMB>(comb<COMB>(v[4], v[5]), comb<COMB>(v[6], v[7]));
         tree_insert<3, COMB>(slot, i, comb<COMB>(l, r));
     }
     for (; i < m; ++i)
-        tree_insert<0, COMB>(slot, i, TV::ld(leaf(i)));
+        tree_insert<0, COMB>(slot, i, leaf(i));
     // merge the occupied slots, smallest (rightmost) first
     T acc{};
     bool have = false;
 #pragma unroll
-    for (int j = 0; j < kTreeSlots; ++j) {
+    for (int j = 0; j < N; ++j) {
         if (m & (1u << j)) {
             acc = have ? comb<COMB>(slot[j], acc) : slot[j];
             have = true;
         }
     }
-    TV::st(a.out + (uint64_t)c * a.len + col, acc);
+    return acc;
+}
+
+template <uint32_t COMB>
+__global__ __launch_bounds__(kBlock) void k_tree(TreeArgs a)
+{
+    typedef TreeVec<4> TV;
+    const uint64_t q = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (4 * q >= a.len)
+        return; // no barriers below
+    uint32_t skip;
+    const uint64_t col = tree_col<4>(q, a.len, skip);
+    const uint32_t c = blockIdx.y;
+    const uint32_t k0 = c * a.chunk;
+    const uint32_t m = min(a.count - k0, a.chunk);
+    const float4 acc = tree_fold<COMB, kTreeSlots, float4>(m, [&](uint32_t i) {
+        const uint32_t kk = k0 + i;
+        return TV::ld((a.ptrs ? a.ptrs[kk] : a.base + (uint64_t)kk * a.stride) + col);
+    });
+    TV::st(a.out + (uint64_t)c * a.len + col, acc, skip);
+}
+
+// Short arrays (at most kTreeFlatThreads vector columns): the threads of a
+// block are `groups` groups (a power of two) of one thread per vector column
+// of the block's `cols`, group g folds leaves [g * per, (g + 1) * per) of the
+// block's chunk, and the groups' trees are combined pairwise through LDS.
+// With one thread per column alone, arrays shorter than a block's threads
+// leave most lanes idle and give each live one a long serial chain.  Bound by
+// HBM or the memory-side cache for large inputs, by the launches and the last
+// pass (one block) below some 20 MB.  Measured on MI355X, before and now:
+// 2^20 rows of 24 floats 279 -> 28 us, of 64 176 -> 49 us, of 255 237 -> 233
+// us; 4000 rows of 1024 floats 29 -> 10 us.  The rows of a group are
+// neighbours, so the loads of its 8 steps share cache lines and repeated
+// inputs stay in the memory-side cache: plain loads, except NT, for inputs
+// that exceed that cache (2^20 rows of 64 floats, 256 MiB: 57 us plain, 68
+// nontemporal; 131072 rows of 2047, 1 GiB: 217 and 206).
+constexpr int kTreeFlatSlots = 7; // up to 2^6 leaves per group
+static_assert(kTreeFlatPer == 1u << (kTreeFlatSlots - 1), "a group's leaves fit the counter");
+
+template <int V, uint32_t COMB, bool NT>
+__global__ __launch_bounds__(kTreeFlatThreads) void k_tree_flat(TreeArgs a)
+{
+    typedef TreeVec<V> TV;
+    typedef typename TV::T T;
+    __shared__ T part[kTreeFlatThreads];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t g = tid / a.cols;
+    const uint32_t q = blockIdx.y * a.cols + (tid - g * a.cols);
+    // the block is rounded up to whole waves, the last column tile is ragged
+    const bool live = g < a.groups && (uint64_t)q * V < a.len;
+    uint32_t skip;
+    const uint64_t col = tree_col<V>(live ? q : 0, a.len, skip);
+    const uint32_t per = a.chunk / a.groups;
+    const uint32_t k0 = blockIdx.x * a.chunk;
+    const uint32_t mb = min(a.count - k0, a.chunk);
+    const uint32_t g0 = g * per;
+    const uint32_t m = live && g0 < mb ? min(per, mb - g0) : 0;
+    T acc = tree_fold<COMB, kTreeFlatSlots, T>(m, [&](uint32_t i) -> T {
+        const uint32_t kk = k0 + g0 + i;
+        const float *p = (a.ptrs ? a.ptrs[kk] : a.base + (uint64_t)kk * a.stride) + col;
+        if constexpr (NT) {
+            return TV::ld(p);
+        } else if constexpr (V == 4) {
+            const f4a4 v = *(gf4u *)p;
+            return make_float4(v.x, v.y, v.z, v.w);
+        } else {
+            return *(gf1 *)p;
+        }
+    });
+    part[tid] = acc;
+    const uint32_t used = (mb + per - 1) / per; // groups that hold leaves
+    for (uint32_t s = 1; s < a.groups; s <<= 1) {
+        __syncthreads();
+        if (live && (g & (2 * s - 1)) == 0 && g + s < used) {
+            acc = comb<COMB>(acc, part[tid + s * a.cols]);
+            part[tid] = acc;
+        }
+    }
+    if (live && g == 0)
+        TV::st(a.out + (uint64_t)blockIdx.x * a.len + col, acc, skip);
 }
 
 // Wide variant (float4 columns only): a thread owns CPT float4 columns BT
@@ -1276,26 +1369,29 @@ __device__ __forceinline__ void tree_insert_cols(float4 (&slot)[kTreeWideSlots][
 template <uint32_t COMB, int CPT, int BT>
 __global__ __launch_bounds__(BT) void k_tree_wide(TreeArgs a)
 {
-    const uint64_t nq = a.len >> 2;
+    const uint64_t nq = (a.len + 3) >> 2;
     const uint64_t q0 = (uint64_t)blockIdx.x * BT * CPT + threadIdx.x;
     if (q0 >= nq)
         return; // no barriers below
+    // the array's last quad may start up to 3 floats early
     bool ok[CPT];
+    uint32_t skip[CPT];
+    uint64_t col[CPT];
 #pragma unroll
-    for (int c = 0; c < CPT; ++c)
-        ok[c] = q0 + (uint64_t)c * BT < nq;
+    for (int c = 0; c < CPT; ++c) {
+        const uint64_t q = q0 + (uint64_t)c * BT;
+        ok[c] = q < nq;
+        col[c] = tree_col<4>(min(q, nq - 1), a.len, skip[c]);
+    }
     const uint32_t ch = blockIdx.y;
     const uint32_t k0 = ch * a.chunk;
     const uint32_t m = min(a.count - k0, a.chunk);
-    auto leaf = [&](uint32_t i) -> const float * {
-        const uint32_t kk = k0 + i;
-        return (a.ptrs ? a.ptrs[kk] : a.base + (uint64_t)kk * a.stride) + 4 * q0;
-    };
     auto load = [&](uint32_t i, float4 (&v)[CPT]) {
-        const float *p = leaf(i);
+        const uint32_t kk = k0 + i;
+        const float *p = a.ptrs ? a.ptrs[kk] : a.base + (uint64_t)kk * a.stride;
 #pragma unroll
         for (int c = 0; c < CPT; ++c)
-            v[c] = ok[c] ? ld4u(p + 4 * (uint64_t)c * BT) : float4{};
+            v[c] = ok[c] ? ld4u(p + col[c]) : float4{};
     };
     float4 slot[kTreeWideSlots][CPT];
     uint32_t i = 0;
@@ -1324,11 +1420,11 @@ __global__ __launch_bounds__(BT) void k_tree_wide(TreeArgs a)
             have = true;
         }
     }
-    float *o = a.out + (uint64_t)ch * a.len + 4 * q0;
+    float *o = a.out + (uint64_t)ch * a.len;
 #pragma unroll
     for (int c = 0; c < CPT; ++c)
         if (ok[c])
-            st4u(o + 4 * (uint64_t)c * BT, acc[c]);
+            TreeVec<4>::st(o + col[c], acc[c], skip[c]);
 }
 
 __global__ __launch_bounds__(kBlock) void k_zero(uint32_t *p, uint64_t words)
@@ -2188,30 +2284,55 @@ int wordcount_blocks_per_cu(int *out)
         out, reinterpret_cast<const void *>(k_wordcount), kBlock, 0));
 }
 
-int launch_tree(const TreeArgs &a, uint32_t combiner, bool vec4, void *stream)
+int launch_tree(const TreeArgs &a, uint32_t combiner, void *stream)
 {
-    if (a.len == 0 || a.count == 0 || a.chunk == 0)
+    if (a.len == 0 || a.count == 0 || a.chunk == 0 ||
+        (combiner != SPARKCL_VADD && combiner != SPARKCL_VMAX))
         return SPARKCL_EINVAL;
-    const uint32_t nchunks = (a.count + a.chunk - 1) / a.chunk;
+    const uint32_t nchunks = (uint32_t)(((uint64_t)a.count + a.chunk - 1) / a.chunk);
     if (nchunks > 1 && (a.chunk & (a.chunk - 1)))
         return SPARKCL_EINVAL;
-    if (a.chunk > (1u << (kTreeSlots - 1)) || nchunks > 65535)
-        return SPARKCL_EINVAL;
-    if (vec4 && (a.len & 3u))
-        return SPARKCL_EINVAL;
+    const bool add = combiner == SPARKCL_VADD;
     hipStream_t s = (hipStream_t)stream;
+    if (a.groups != 0) {
+        const uint64_t ncol = a.len < 4 ? a.len : (a.len + 3) / 4;
+        const uint64_t tiles = a.cols ? (ncol + a.cols - 1) / a.cols : 0;
+        if (tiles == 0 || tiles > 65535 || (a.groups & (a.groups - 1)) || a.chunk % a.groups ||
+            ((a.chunk / a.groups) & (a.chunk / a.groups - 1)) ||
+            a.chunk / a.groups > kTreeFlatPer ||
+            (uint64_t)a.cols * a.groups > a.threads || a.threads > kTreeFlatThreads || a.threads % 64)
+            return SPARKCL_EINVAL;
+        const dim3 grid(nchunks, (uint32_t)tiles), block(a.threads);
+        const bool nt = a.len >= 4 && a.len * a.count * 4 > kTreeCached;
+#define SPARKCL_FLAT(V, NT)                                                    \
+    do {                                                                       \
+        if (add)                                                               \
+            hipLaunchKernelGGL((k_tree_flat<V, SPARKCL_VADD, NT>), grid, block, 0, s, a); \
+        else                                                                   \
+            hipLaunchKernelGGL((k_tree_flat<V, SPARKCL_VMAX, NT>), grid, block, 0, s, a); \
+    } while (0)
+        if (a.len < 4)
+            SPARKCL_FLAT(1, false);
+        else if (nt)
+            SPARKCL_FLAT(4, true);
+        else
+            SPARKCL_FLAT(4, false);
+#undef SPARKCL_FLAT
+        return hip_status(hipGetLastError());
+    }
+    if (a.len < 4 || a.chunk > (1u << (kTreeSlots - 1)) || nchunks > 65535)
+        return SPARKCL_EINVAL;
     if (a.cpt != 1) {
-        if (!vec4 || (a.cpt != 2 && a.cpt != 4) || a.chunk > kTreeWideChunk ||
-            (combiner != SPARKCL_VADD && combiner != SPARKCL_VMAX) ||
+        if ((a.cpt != 2 && a.cpt != 4) || a.chunk > kTreeWideChunk ||
             (a.threads != (uint32_t)kBlock && !(a.threads == kTreeWideBig && a.cpt == 4)))
             return SPARKCL_EINVAL;
         const uint64_t per_block = (uint64_t)a.threads * a.cpt;
-        const uint64_t cb = ((a.len >> 2) + per_block - 1) / per_block;
+        const uint64_t cb = ((a.len + 3) / 4 + per_block - 1) / per_block;
         if (cb > 0x7fffffffull)
             return SPARKCL_EINVAL;
         const dim3 grid((uint32_t)cb, nchunks);
         const dim3 block(a.threads);
-        if (combiner == SPARKCL_VADD) {
+        if (add) {
             if (a.threads == kTreeWideBig)
                 hipLaunchKernelGGL((k_tree_wide<SPARKCL_VADD, 4, kTreeWideBig>), grid, block, 0, s, a);
             else if (a.cpt == 4)
@@ -2228,24 +2349,14 @@ int launch_tree(const TreeArgs &a, uint32_t combiner, bool vec4, void *stream)
         }
         return hip_status(hipGetLastError());
     }
-    const uint32_t V = vec4 ? 4 : 1;
-    const uint64_t colblocks = (a.len + (uint64_t)kBlock * V - 1) / ((uint64_t)kBlock * V);
+    const uint64_t colblocks = ((a.len + 3) / 4 + kBlock - 1) / kBlock;
     if (colblocks > 0x7fffffffull)
         return SPARKCL_EINVAL;
     const dim3 grid((uint32_t)colblocks, nchunks);
-    if (combiner == SPARKCL_VADD) {
-        if (vec4)
-            hipLaunchKernelGGL((k_tree<4, SPARKCL_VADD>), grid, dim3(kBlock), 0, s, a);
-        else
-            hipLaunchKernelGGL((k_tree<1, SPARKCL_VADD>), grid, dim3(kBlock), 0, s, a);
-    } else if (combiner == SPARKCL_VMAX) {
-        if (vec4)
-            hipLaunchKernelGGL((k_tree<4, SPARKCL_VMAX>), grid, dim3(kBlock), 0, s, a);
-        else
-            hipLaunchKernelGGL((k_tree<1, SPARKCL_VMAX>), grid, dim3(kBlock), 0, s, a);
-    } else {
-        return SPARKCL_EINVAL;
-    }
+    if (add)
+        hipLaunchKernelGGL((k_tree<SPARKCL_VADD>), grid, dim3(kBlock), 0, s, a);
+    else
+        hipLaunchKernelGGL((k_tree<SPARKCL_VMAX>), grid, dim3(kBlock), 0, s, a);
     return hip_status(hipGetLastError());
 }
 

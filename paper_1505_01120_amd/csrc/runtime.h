@@ -90,7 +90,6 @@ struct Plan {
     uint32_t combiner = 0;
     uint64_t len = 0;
     float *user_out = nullptr;
-    bool vec4 = false;
     uint32_t nleaves = 0;
     const float *leaf_base = nullptr;
     uint64_t leaf_stride = 0;

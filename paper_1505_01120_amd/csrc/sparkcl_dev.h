@@ -181,11 +181,22 @@ struct TreeArgs {
     uint32_t cpt; // float4 columns per thread: 1 (8-leaf groups), or 2 / 4
                   // (leaf pairs, chunks of at most kTreeWideChunk leaves)
     uint32_t threads; // block threads of the leaf-pair kernel: kBlock, or
-                      // kTreeWideBig with 4 columns per thread
+                      // kTreeWideBig with 4 columns per thread; of the
+                      // short-array kernel: whole waves that hold its groups
+    uint32_t groups;  // short arrays: thread groups of a block (a power of
+                      // two), chunk / groups leaves each; else 0
+    uint32_t cols;    // vector columns of a block of the short-array kernel
 };
 constexpr uint32_t kTreeWideChunk = 64;
 constexpr uint32_t kTreeWideBig = 512;
-int launch_tree(const TreeArgs &a, uint32_t combiner, bool vec4, void *stream);
+// The short-array kernel: vector columns (float4, or floats of arrays shorter
+// than 4) an array may have, which is also the most threads of a block, and
+// leaves a thread folds at most; the memory-side cache's size, past which its
+// loads are nontemporal.
+constexpr uint32_t kTreeFlatThreads = 1024;
+constexpr uint32_t kTreeFlatPer = 64;
+constexpr uint64_t kTreeCached = 256ull << 20;
+int launch_tree(const TreeArgs &a, uint32_t combiner, void *stream);
 // WordCount: text of n bytes counted into the global open-addressing table
 // keys/counts of mask + 1 slots (a power of two, cleared beforehand); ctl[0]
 // words, ctl[1] count of the key 0, ctl[2] table-full flag, ctl[3] distinct
