@@ -1438,33 +1438,42 @@ __global__ __launch_bounds__(kBlock) void k_zero(uint32_t *p, uint64_t words)
 // The word-count demo (sec. 3.2.3) as a partition kernel over a byte stream:
 // a word is a maximal run of non-whitespace bytes, counted under the 64-bit
 // FNV-1a hash of its bytes (Fowler, Noll, Vo: xor the byte in, multiply by
-// the 64-bit FNV prime).  Blocks stage 4 KiB chunks of text (plus a 256-byte
-// look-ahead) in LDS; the thread owning a word's first byte hashes it and
-// counts it in the block's LDS hash table (the paper's "local data"), which
-// absorbs the frequent words of a skewed vocabulary.  Words that find no
-// LDS slot within a few probes are appended to the block's spill region of
-// their key's partition (a plain store at an LDS-counted position); a merge
-// kernel then counts each partition's spilled keys in LDS and adds each
-// distinct key once to the global open-addressing table.  (Adding every such word to the global table
-// with a device-scope atomic, as a first version did, cost more than the
-// scan: those atomics are carried out at the memory side, one round trip
-// each.)  The LDS tables themselves, and the words that overflow a spill
-// region, go to the table with atomics.  Counts are integers, so the result
-// does not depend on which block counts which word.
-constexpr uint32_t kWcChunk = 4096;   // bytes per chunk: 16 per thread
-constexpr uint32_t kWcLook = 256;     // look-ahead bytes staged after a chunk
-constexpr uint32_t kWcSlots = 2048;   // LDS hash slots per block
-constexpr uint32_t kWcProbes = 2;     // LDS probes before a word spills
-static_assert(kWcChunk == 16 * kBlock, "one 16-byte span per thread");
+// the 64-bit FNV prime).  Every lane walks a span of the text, all lanes in
+// step, and keeps the running hash in registers; a word belongs to the lane
+// whose span holds its first byte, which follows it past the span's end.  The
+// words that end at a step go to a queue of the wave in LDS, which is emptied
+// 64 words at a time, all lanes busy, into the block's LDS hash table (the
+// paper's "local data").  The table absorbs the frequent words of a skewed
+// vocabulary; a word that finds no place in its set is appended to the
+// block's spill region of its key's partition (a plain store at an
+// LDS-counted position); a merge kernel then counts each partition's spilled
+// keys in LDS and adds each distinct key once to the global open-addressing
+// table.  (Adding every such word to the global table with a device-scope
+// atomic cost more than the scan: those atomics are carried out at the memory
+// side, one round trip each.)  The LDS tables themselves, and the words that
+// overflow a spill region, go to the table with atomics.  Counts are integers,
+// so the result does not depend on which block counts which word.
+//
+// One block of 16 waves per CU shares one table of 8192 keys: four blocks of
+// 2048 keys each would hold the same few frequent words four times over.
+//
+// Measured on MI355X, 512 MiB of Zipf text (10^5 words), whole call with its
+// sort of the keys: 1400-1575 us with one word per lane hashed byte by byte
+// from LDS and the tables added to the global one by atomics, 643 us so; 256
+// MiB of 2 10^5 words 4350 and 455 us.  Of the scan's 435 us its walk takes 320
+// without a word kept; places 55; the second queue and the tables written
+// out whole took 150 off what misses and atomics cost.
+constexpr int kWcBlock = (int)kWcWaves * 64;
+constexpr uint32_t kWcQueue = 64 + 4 * 64; // a wave's waiting words: 8 steps end
+                                           // at most 4 per lane
+constexpr uint32_t kWcMissed = 2 * 64;     // those that found no place in the table
+constexpr uint32_t kWcPartSets = kWcSets >> kWcPartBits;
+// Locating keeps offsets beside the words, so its table is smaller.
+constexpr uint32_t kWlSets = 3072;
 
 __device__ __forceinline__ bool wc_space(uint32_t b)
 {
     return b == 0x20u || (b - 0x09u) <= 4u; // space, tab, LF, VT, FF, CR
-}
-
-__device__ __forceinline__ uint64_t fnv_step(uint64_t h, uint32_t b)
-{
-    return (h ^ (uint64_t)b) * 1099511628211ull;
 }
 
 // Add c to key h in the global table (keys 0 = empty; a word whose hash is 0
@@ -1505,9 +1514,8 @@ __device__ void wc_global_add(const WcArgs &a, uint64_t h, uint64_t c)
 }
 
 // The LDS counts are 32-bit: a block counts at most one word per two bytes
-// of the text it scans, and a block scans either one 4 KiB chunk or at most
-// 1/256 of the text (a grid of at least one block per CU), which is limited
-// to 2^40 bytes.
+// of the text it scans, and a block scans either a few KiB or about 1/256 of
+// the text (a grid of one block per CU), which is limited to 2^40 bytes.
 // A word that found no LDS slot: appended to this block's spill region of
 // its partition, or, when the region is full (or there are none, or its key
 // is 0), added to the table directly.  scnt: the block's per-partition
@@ -1515,7 +1523,7 @@ __device__ void wc_global_add(const WcArgs &a, uint64_t h, uint64_t c)
 __device__ __forceinline__ void wc_spill(uint32_t *scnt, const WcArgs &a, uint64_t h)
 {
     if (a.spill_cap != 0 && h != 0) {
-        const uint32_t p = (uint32_t)(h >> (64 - kWcPartBits));
+        const uint32_t p = ((uint32_t)h & (kWcSets - 1)) / kWcPartSets;
         const uint32_t pos = atomicAdd(&scnt[p], 1u);
         if (pos < a.spill_cap) {
             a.spill[((uint64_t)blockIdx.x << kWcPartBits | p) * a.spill_cap + pos] = h;
@@ -1525,365 +1533,691 @@ __device__ __forceinline__ void wc_spill(uint32_t *scnt, const WcArgs &a, uint64
     wc_global_add(a, h, 1);
 }
 
-__device__ __forceinline__ void wc_local_add(uint64_t *sk, uint32_t *sc, uint32_t *scnt,
-                                             const WcArgs &a, uint64_t h)
+// The place of key h in an LDS table of two-key sets: the slot that holds it
+// or, if a way of its set is free, takes it; else kNoSlot.  Keys are only ever
+// added, so a key read as equal stays.
+constexpr uint32_t kNoSlot = ~0u;
+__device__ __forceinline__ uint32_t wc_place(uint64_t *sk, uint32_t set, uint64_t h)
 {
-    if (h != 0) {
-        uint32_t s = (uint32_t)h & (kWcSlots - 1);
-        for (uint32_t p = 0; p < kWcProbes; ++p) {
-            const uint64_t k = sk[s];
-            if (k == h) {
-                atomicAdd(&sc[s], 1u);
-                return;
-            }
-            if (k == 0) {
-                const uint64_t old =
-                    atomicCAS((unsigned long long *)&sk[s], 0ull, (unsigned long long)h);
-                if (old == 0 || old == h) {
-                    atomicAdd(&sc[s], 1u);
-                    return;
-                }
-            }
-            s = (s + 1) & (kWcSlots - 1);
+    const uint32_t s = 2 * set;
+    const ulonglong2 k = *reinterpret_cast<const ulonglong2 *>(sk + s);
+    const bool second = k.y == h;
+    uint32_t at = k.x == h || second ? s + (second ? 1u : 0u) : kNoSlot;
+    if (at == kNoSlot && (k.x == 0 || k.y == 0)) {
+        // a free way, seldom once the table has filled
+        for (uint32_t w = 0; w < 2 && at == kNoSlot; ++w) {
+            const uint64_t old =
+                atomicCAS((unsigned long long *)&sk[s + w], 0ull, (unsigned long long)h);
+            if (old == 0 || old == h)
+                at = s + w;
         }
     }
-    wc_spill(scnt, a, h);
+    return at;
 }
 
-// 16 bytes of text at byte `pos` (a thread's span), bytes at or past n read
-// as spaces, so no word starts or continues there.
-__device__ __forceinline__ uint4 wc_span(const uint8_t *text, uint64_t n, uint64_t pos,
-                                         bool vec)
+// 16 bytes of text at byte `pos`, whatever its alignment (the memory pipeline
+// takes unaligned 16-byte loads).
+// Kept as vectors, and not as structs of four words, so that a load's result
+// stays where it arrives.
+typedef uint32_t wc_u4 __attribute__((ext_vector_type(4)));
+typedef uint32_t wc_u4a1 __attribute__((ext_vector_type(4), aligned(1)));
+typedef __attribute__((address_space(1))) const wc_u4a1 wc_gu4;
+typedef __attribute__((address_space(1))) const uint8_t wc_gu1;
+__device__ __forceinline__ wc_u4 wc_span(const uint8_t *text, uint64_t pos)
 {
-    if (vec && pos + 16 <= n)
-        return *reinterpret_cast<const uint4 *>(text + pos);
-    uint32_t w[4] = {0x20202020u, 0x20202020u, 0x20202020u, 0x20202020u};
-#pragma unroll
-    for (int k = 0; k < 16; ++k)
-        if (pos + k < n) {
-            const uint32_t sh = 8 * (k & 3);
-            w[k >> 2] = (w[k >> 2] & ~(0xFFu << sh)) | ((uint32_t)text[pos + k] << sh);
-        }
-    return make_uint4(w[0], w[1], w[2], w[3]);
+    return *(wc_gu4 *)(text + pos);
+}
+// The bytes of the 16 at `pos` of a text of n >= 16 that lie before n, the
+// others spaces, so that no word starts or goes on there: v is what stands at
+// min(pos, n - 16), moved down as differences from spaces.
+__device__ __forceinline__ wc_u4 wc_span_end(const wc_u4 &v, uint64_t n, uint64_t pos)
+{
+    constexpr uint64_t kSpaces = 0x2020202020202020ull;
+    uint64_t lo = ((uint64_t)v.y << 32 | v.x) ^ kSpaces;
+    uint64_t hi = ((uint64_t)v.w << 32 | v.z) ^ kSpaces;
+    uint32_t by = pos > n - 16 ? (uint32_t)min(pos - (n - 16), (uint64_t)16) : 0u;
+    if (by >= 8) {
+        lo = hi;
+        hi = 0;
+        by -= 8;
+    }
+    if (by >= 8) {
+        lo = 0;
+    } else if (by > 0) {
+        lo = lo >> (8 * by) | hi << (64 - 8 * by);
+        hi >>= 8 * by;
+    }
+    lo ^= kSpaces;
+    hi ^= kSpaces;
+    return wc_u4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
 }
 
-// Bit i of the result is set when byte i of w (little-endian) is whitespace
-// (wc_space), for the four bytes at once: with each byte's top bit forced to
-// 1, the per-byte subtractions below cannot borrow across bytes, so the top
-// bit of each byte of (w | 0x80..) - c tells whether its low 7 bits are >= c;
-// bytes of 0x80 and above are never whitespace.
-__device__ __forceinline__ uint32_t space_bits4(uint32_t w)
+// The top bit of every byte of w that is whitespace (wc_space), the other bits
+// clear: with each byte's top bit forced to 1, the per-byte subtractions
+// cannot borrow across bytes, so the top bit of each byte of
+// (w | 0x80..) - c tells whether its low 7 bits are >= c; bytes of 0x80 and
+// above are never whitespace.
+__device__ __forceinline__ uint32_t wc_space_tops(uint32_t w)
 {
     const uint32_t top = 0x80808080u;
     const uint32_t up = w | top;
-    const uint32_t ge09 = (up - 0x09090909u) & top;
-    const uint32_t ge0e = (up - 0x0E0E0E0Eu) & top;
-    const uint32_t ne20 = (((w ^ 0x20202020u) & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) & top;
-    const uint32_t ws = ((ge09 & ~ge0e) | (~ne20 & top)) & ~w & top;
-    return ((ws >> 7) & 1u) | ((ws >> 14) & 2u) | ((ws >> 21) & 4u) | ((ws >> 28) & 8u);
+    const uint32_t ge09 = up - 0x09090909u;
+    const uint32_t ge0e = up - 0x0E0E0E0Eu;
+    const uint32_t ne20 = ((w ^ 0x20202020u) & 0x7F7F7F7Fu) + 0x7F7F7F7Fu;
+    return ((ge09 & ~ge0e) | ~ne20) & ~w & top;
 }
 
-// Block barrier for LDS traffic only: waits for this wave's LDS operations,
-// not for its global loads in flight (the next chunk's prefetch).
-__device__ __forceinline__ void lds_barrier()
+// Byte K of w: the mask of lanes in which it is not 0 / a ^ it.  One vector
+// instruction each (the byte select is an operand modifier).  The first needs
+// every lane active; a vector instruction may read its scalar result no
+// earlier than two wait states on, which the compiler cannot see to here:
+// masks_ready() stands between.
+template <int K> __device__ __forceinline__ uint64_t byte_mask(uint32_t w, uint32_t zero)
 {
-    __asm__ __volatile__("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xC07F); // lgkmcnt(0); vmcnt, expcnt untouched
-    __builtin_amdgcn_s_barrier();
-    __asm__ __volatile__("" ::: "memory");
+    uint64_t r;
+#define SPARKCL_BYTE_MASK(B)                                                   \
+    __asm__ volatile("v_cmp_ne_u32_sdwa %0, %1, %2 src0_sel:" B " src1_sel:DWORD" \
+                     : "=s"(r) : "v"(w), "v"(zero))
+    if constexpr (K == 0)
+        SPARKCL_BYTE_MASK("BYTE_0");
+    else if constexpr (K == 1)
+        SPARKCL_BYTE_MASK("BYTE_1");
+    else if constexpr (K == 2)
+        SPARKCL_BYTE_MASK("BYTE_2");
+    else
+        SPARKCL_BYTE_MASK("BYTE_3");
+#undef SPARKCL_BYTE_MASK
+    return r;
+}
+__device__ __forceinline__ void masks_ready(uint64_t (&m)[8])
+{
+    __asm__ volatile("s_nop 1" : "+s"(m[0]), "+s"(m[1]), "+s"(m[2]), "+s"(m[3]), "+s"(m[4]),
+                                 "+s"(m[5]), "+s"(m[6]), "+s"(m[7]));
+}
+template <int K> __device__ __forceinline__ uint32_t xor_byte(uint32_t a, uint32_t w)
+{
+    uint32_t r;
+    if constexpr (K == 0)
+        __asm__("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD "
+                "src0_sel:DWORD src1_sel:BYTE_0" : "=v"(r) : "v"(a), "v"(w));
+    else if constexpr (K == 1)
+        __asm__("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD "
+                "src0_sel:DWORD src1_sel:BYTE_1" : "=v"(r) : "v"(a), "v"(w));
+    else if constexpr (K == 2)
+        __asm__("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD "
+                "src0_sel:DWORD src1_sel:BYTE_2" : "=v"(r) : "v"(a), "v"(w));
+    else
+        __asm__("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD "
+                "src0_sel:DWORD src1_sel:BYTE_3" : "=v"(r) : "v"(a), "v"(w));
+    return r;
 }
 
-// The scan.  Per staged chunk: each thread marks the whitespace bytes of its
-// 16-byte span in a bitmap (one 16-bit word per span, chunk and look-ahead)
-// and the word starts in its span; a wave prefix sum places the starts in a
-// per-wave list; then each lane takes whole words from the list, reads the
-// word's length off the bitmap, hashes its bytes from the staged chunk and
-// counts the key in the block's LDS table.  A word that runs past the
-// look-ahead continues from the text in global memory, one byte at a time.
-// The scan front end shared by counting and locating: the block's chunks of
-// the text are staged in LDS, each wave lists its words' starts and hashes
-// one word per lane; word(h, off) is called with the word's key and the byte
-// offset of its first byte.  Returns the number of words this thread listed.
-template <class Word>
-__device__ __forceinline__ uint64_t wc_scan(const uint8_t *text, uint64_t n, Word word)
+// to <- from before any load that follows.  Left to itself the compiler issues
+// the loads that refill `from` first, into other registers, and then waits for
+// them to copy them into place.
+__device__ __forceinline__ void wc_take(wc_u4 (&to)[4], const wc_u4 (&from)[4])
 {
-    constexpr uint32_t kLookSpans = kWcLook / 16;
-    constexpr uint32_t kSpans = kBlock + kLookSpans;
-    __shared__ uint4 st4[kSpans + 1];               // (+ 16 bytes read past the end)
-    __shared__ uint32_t sepm[kSpans];               // whitespace bits of each span
-    __shared__ uint16_t starts16[kWaves][64 * 8];   // a 16-byte span holds <= 8 word starts
-    __shared__ uint32_t sh_prev;
-    const uint8_t *st = reinterpret_cast<const uint8_t *>(st4);
-    if (threadIdx.x == 0)
-        st4[kSpans] = make_uint4(0x20202020u, 0x20202020u, 0x20202020u, 0x20202020u);
-    const bool vec = ((uintptr_t)text & 15u) == 0;
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    uint16_t *wl = starts16[wave];
-    const uint64_t nchunks = (n + kWcChunk - 1) / kWcChunk;
-    constexpr uint64_t kBasis = 14695981039346656037ull;
-    // this thread's span of the first chunk, its look-ahead span and (thread
-    // 0) the byte before the chunk, loaded ahead of use
-    uint64_t c = blockIdx.x;
-    uint4 cur = wc_span(text, n, c * kWcChunk + 16 * tid, vec);
-    uint4 look = make_uint4(0, 0, 0, 0);
-    if (tid < kLookSpans)
-        look = wc_span(text, n, c * kWcChunk + kWcChunk + 16 * tid, vec);
-    uint32_t prevb = (tid == 0 && c > 0 && c < nchunks) ? text[c * kWcChunk - 1] : 0x20u;
-    uint64_t words = 0;
-    for (; c < nchunks; c += gridDim.x) {
-        const uint64_t c0 = c * kWcChunk;
-        lds_barrier(); // the previous chunk's words are done with the staging
-        const uint4 mine = cur;
-        st4[tid] = mine;
-        const uint32_t sep = space_bits4(mine.x) | (space_bits4(mine.y) << 4) |
-                             (space_bits4(mine.z) << 8) | (space_bits4(mine.w) << 12);
-        sepm[tid] = sep;
-        if (tid < kLookSpans) {
-            st4[kBlock + tid] = look;
-            sepm[kBlock + tid] = space_bits4(look.x) | (space_bits4(look.y) << 4) |
-                                 (space_bits4(look.z) << 8) | (space_bits4(look.w) << 12);
-        }
-        if (tid == 0)
-            sh_prev = prevb;
-        const uint64_t cn = c + gridDim.x;
-        if (cn < nchunks) { // prefetch the block's next chunk
-            cur = wc_span(text, n, cn * kWcChunk + 16 * tid, vec);
-            if (tid < kLookSpans)
-                look = wc_span(text, n, cn * kWcChunk + kWcChunk + 16 * tid, vec);
-            if (tid == 0)
-                prevb = text[cn * kWcChunk - 1];
-        }
-        lds_barrier(); // staged
-        const uint32_t prev = tid ? st[16 * tid - 1] : sh_prev;
-        uint32_t starts = ~sep & ((sep << 1) | (uint32_t)wc_space(prev)) & 0xFFFFu;
-        const uint32_t mycount = __builtin_popcount(starts);
-        // exclusive prefix sum of the word counts over the wave's lanes
-        uint32_t incl = mycount;
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t v = __shfl_up(incl, o);
-            if (lane >= (uint32_t)o)
-                incl += v;
+    for (int u = 0; u < 4; ++u) {
+        to[u] = from[u];
+        __asm__ volatile("" : "+v"(to[u]) : : "memory");
+    }
+}
+
+// a in the lanes of the mask, b in the others.
+__device__ __forceinline__ uint32_t lanes_select(uint64_t mask, uint32_t a, uint32_t b)
+{
+    uint32_t r;
+    __asm__("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(mask));
+    return r;
+}
+
+// A wave's walk: the lanes' running hashes, and for all lanes at once whether
+// a word of the lane's is open and whether the lane may not start one: before
+// its span's first whitespace, in a word of the lane before, and past its
+// span's end.
+template <bool kOff> struct WcWalk {
+    uint32_t lo, hi;
+    uint32_t start;  // kOff: where the open word starts, from the chunk's start
+    uint64_t open, dead;
+    uint32_t top;    // LDS address of the queue's first free key
+    uint32_t top_off; // kOff: of its first free offset
+};
+constexpr uint32_t kFnvLo = 0x84222325u, kFnvHi = 0xCBF29CE4u;
+
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+__device__ __forceinline__ uint32_t lds_address(const void *p)
+{
+    return (uint32_t)(uintptr_t)(lds_u32 *)(void *)p;
+}
+
+// Four stores, each of the lanes in its mask, all lanes active before and
+// after; without a branch around each store.
+__device__ __forceinline__ void lds_store4(const uint64_t *mask, const uint32_t *at,
+                                           const uint32_t *lo, const uint32_t *hi)
+{
+    __asm__ volatile("s_mov_b64 exec, %0\n\t"
+                     "ds_write2_b32 %4, %8, %12 offset1:1\n\t"
+                     "s_mov_b64 exec, %1\n\t"
+                     "ds_write2_b32 %5, %9, %13 offset1:1\n\t"
+                     "s_mov_b64 exec, %2\n\t"
+                     "ds_write2_b32 %6, %10, %14 offset1:1\n\t"
+                     "s_mov_b64 exec, %3\n\t"
+                     "ds_write2_b32 %7, %11, %15 offset1:1\n\t"
+                     "s_mov_b64 exec, -1"
+                     : : "s"(mask[0]), "s"(mask[1]), "s"(mask[2]), "s"(mask[3]), "v"(at[0]),
+                         "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(lo[0]), "v"(lo[1]), "v"(lo[2]),
+                         "v"(lo[3]), "v"(hi[0]), "v"(hi[1]), "v"(hi[2]), "v"(hi[3])
+                     : "memory");
+}
+__device__ __forceinline__ void lds_store4_u16(const uint64_t *mask, const uint32_t *at,
+                                               const uint32_t *v)
+{
+    __asm__ volatile("s_mov_b64 exec, %0\n\t"
+                     "ds_write_b16 %4, %8\n\t"
+                     "s_mov_b64 exec, %1\n\t"
+                     "ds_write_b16 %5, %9\n\t"
+                     "s_mov_b64 exec, %2\n\t"
+                     "ds_write_b16 %6, %10\n\t"
+                     "s_mov_b64 exec, %3\n\t"
+                     "ds_write_b16 %7, %11\n\t"
+                     "s_mov_b64 exec, -1"
+                     : : "s"(mask[0]), "s"(mask[1]), "s"(mask[2]), "s"(mask[3]), "v"(at[0]),
+                         "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(v[0]), "v"(v[1]), "v"(v[2]),
+                         "v"(v[3])
+                     : "memory");
+}
+
+// Takes byte K of w into the hash, (h ^ b) * (2^40 + 435) mod 2^64, or starts
+// over in the lanes of `sep`.
+template <int K>
+__device__ __forceinline__ void fnv_step(uint32_t &lo, uint32_t &hi, uint32_t w, uint64_t sep)
+{
+    const uint32_t x = xor_byte<K>(lo, w);
+    const uint64_t p = (uint64_t)x * 435u;
+    lo = lanes_select(sep, kFnvLo, (uint32_t)p);
+    hi = lanes_select(sep, kFnvHi, hi * 435u + (x << 8) + (uint32_t)(p >> 32));
+}
+
+// Eight steps, the bytes of w0 and w1 in every lane: lanes that read whitespace
+// with a word open queue the word's key; every hash takes the byte in or starts
+// over after whitespace.  kPast: past the spans, where only open words go on.
+// The masks of all steps come first, then the queue positions, then the
+// hashes, then the stores: step by step, each step's vector -> scalar ->
+// vector chain was waited for.
+template <bool kOff, bool kPast>
+__device__ __forceinline__ void wc_steps(WcWalk<kOff> &s, uint32_t w0, uint32_t w1, uint32_t zero,
+                                         uint32_t at)
+{
+    const uint32_t s0 = wc_space_tops(w0), s1 = wc_space_tops(w1);
+    uint64_t sep[8] = {byte_mask<0>(s0, zero), byte_mask<1>(s0, zero),
+                       byte_mask<2>(s0, zero), byte_mask<3>(s0, zero),
+                       byte_mask<0>(s1, zero), byte_mask<1>(s1, zero),
+                       byte_mask<2>(s1, zero), byte_mask<3>(s1, zero)};
+    masks_ready(sep);
+    uint64_t ends[8];
+    uint32_t pos[8], start[8], off[8], lo[8], hi[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        ends[k] = sep[k] & s.open;
+        if constexpr (kOff)
+            start[k] = s.start; // of the word that ends here
+        if constexpr (kPast) {
+            s.open &= ~sep[k];
+        } else {
+            const uint64_t was = s.open;
+            s.dead &= ~sep[k];
+            s.open = ~(sep[k] | s.dead);
+            if constexpr (kOff)
+                s.start = lanes_select(s.open & ~was, at + k, s.start);
         }
-        const uint32_t total = __shfl(incl, 63);
-        uint32_t slot = incl - mycount;
-        while (starts) {
-            const uint32_t b = __builtin_ctz(starts);
-            wl[slot++] = (uint16_t)(16 * tid + b);
-            starts &= starts - 1;
+        const uint32_t before = __builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(ends[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ends[k], 0u));
+        const uint32_t count = (uint32_t)__popcll(ends[k]);
+        pos[k] = s.top + 8 * before;
+        s.top += 8 * count;
+        __asm__("" : "+s"(s.top)); // keeps the address one shift-add
+        if constexpr (kOff) {
+            off[k] = s.top_off + 2 * before;
+            s.top_off += 2 * count;
+            __asm__("" : "+s"(s.top_off));
         }
-        words += mycount;
-        // the wave's words: one per lane at a time
-        for (uint32_t i = lane; i < total; i += 64) {
-            const uint32_t s0 = wl[i];
-            // length: the distance to the next whitespace bit at or after s0
-            uint32_t span = s0 >> 4;
-            uint32_t m = sepm[span] >> (s0 & 15u);
-            uint32_t len = 0;
-            bool ends = m != 0;
-            if (ends) {
-                len = __builtin_ctz(m);
-            } else {
-                len = 16u - (s0 & 15u);
-                for (++span; span < kSpans; ++span) {
-                    m = sepm[span];
-                    if (m) {
-                        len += __builtin_ctz(m);
-                        ends = true;
-                        break;
+    }
+#define SPARKCL_WC_HASH(k, W)                                                  \
+    lo[k] = s.lo;                                                              \
+    hi[k] = s.hi;                                                              \
+    fnv_step<(k) & 3>(s.lo, s.hi, W, sep[k]);
+    SPARKCL_WC_HASH(0, w0)
+    SPARKCL_WC_HASH(1, w0)
+    SPARKCL_WC_HASH(2, w0)
+    SPARKCL_WC_HASH(3, w0)
+    SPARKCL_WC_HASH(4, w1)
+    SPARKCL_WC_HASH(5, w1)
+    SPARKCL_WC_HASH(6, w1)
+    SPARKCL_WC_HASH(7, w1)
+#undef SPARKCL_WC_HASH
+    lds_store4(ends, pos, lo, hi);
+    lds_store4(ends + 4, pos + 4, lo + 4, hi + 4);
+    if constexpr (kOff) {
+        lds_store4_u16(ends, off, start);
+        lds_store4_u16(ends + 4, off + 4, start + 4);
+    }
+}
+
+// The scan front end shared by counting and locating.  The waves of the grid
+// take chunks of 64 spans of `span` bytes (a multiple of 16, at most
+// kWcMaxSpan) in turn, a wave's chunks in ascending order, neighbours on
+// different CUs; word(h, off) is called with the keys of up to 64 words at a
+// time and, for kOff, the byte offsets of their first bytes.  The words for
+// which it returns true, a minority, are queued once more and handed to
+// missed(count, h, off), again 64 at a time (count: of the lanes, from the
+// first on; all are active): what it costs is then paid by full waves.
+// Returns the number of words this wave saw.
+//
+// Bound by vector-instruction issue: about 13 instructions per step and 64
+// bytes of text (71% of the SIMDs' cycles in the walk alone), and 16 more steps
+// per span for the words that cross its end.  The walk touches no LDS but the
+// queue; chunks of long spans keep those steps and the chunks' starts rare
+// (512 MiB as one span of 2 KiB per lane, 340 us; as eight of 256 bytes, 366).
+template <bool kOff, class Word, class Missed>
+__device__ __forceinline__ uint64_t wc_scan(const uint8_t *text, uint64_t n, uint32_t span,
+                                            Word word, Missed missed)
+{
+    __shared__ uint32_t queue[kWcWaves][2 * kWcQueue]; // keys, low words first
+    __shared__ uint16_t queue_off[kOff ? kWcWaves : 1][kOff ? kWcQueue : 1];
+    __shared__ uint64_t miss_queue[kWcWaves][kWcMissed];
+    __shared__ uint16_t miss_off[kOff ? kWcWaves : 1][kOff ? kWcMissed : 1];
+    const uint32_t lane = threadIdx.x & 63u, wave = uni(threadIdx.x >> 6);
+    const uint32_t *q = queue[wave];
+    const uint16_t *qo = kOff ? queue_off[wave] : nullptr;
+    const uint32_t q0 = uni(lds_address(q)), qo0 = kOff ? uni(lds_address(qo)) : 0;
+    auto key = [&](uint32_t i) -> uint64_t { return (uint64_t)q[2 * i + 1] << 32 | q[2 * i]; };
+    uint64_t *mq = miss_queue[wave];
+    uint16_t *mo = kOff ? miss_off[wave] : nullptr;
+    uint32_t nmiss = 0;
+    auto words64 = [&](bool valid, uint64_t h, uint32_t off, uint64_t c0) {
+        const bool miss = valid && word(h, c0 + off);
+        const uint64_t m = __ballot(miss);
+        if (miss) {
+            const uint32_t at = nmiss + __builtin_amdgcn_mbcnt_hi(
+                (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            mq[at] = h;
+            if (kOff)
+                mo[at] = (uint16_t)off;
+        }
+        nmiss += (uint32_t)__popcll(m);
+        if (nmiss >= 64) {
+            nmiss -= 64;
+            missed(64u, mq[nmiss + lane], kOff ? c0 + mo[nmiss + lane] : 0ull);
+        }
+    };
+    const uint64_t bytes = 64ull * span;
+    const uint64_t nchunks = (n + bytes - 1) / bytes;
+    const uint32_t steps = span / 16;
+    uint32_t zero = 0;
+    __asm__ volatile("v_mov_b32 %0, 0" : "=v"(zero)); // a register, not a constant
+    uint64_t words = 0;
+    WcWalk<kOff> s;
+    s.top = q0;
+    s.top_off = qo0;
+    s.start = 0;
+    // 64 bytes per lane at a time, the next 64 loaded ahead, also those of the
+    // next chunk; what lies past the end is read at the end and put right later
+    const uint64_t last = n - 16;
+    auto load = [&](uint64_t at, wc_u4 (&v)[4]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            v[u] = wc_span(text, min(at + 16 * u, last));
+    };
+    auto byte_before = [&](uint64_t at) -> uint32_t {
+        return at > 0 && at <= n ? *(wc_gu1 *)(text + at - 1) : 0x20u;
+    };
+    const uint64_t c_step = (uint64_t)gridDim.x * kWcWaves;
+    uint64_t c = (uint64_t)wave * gridDim.x + blockIdx.x;
+    wc_u4 cur[4], nx[4], first[4];
+    uint32_t before_next = 0x20u;
+    if (c < nchunks) {
+        load(c * bytes + (uint64_t)lane * span, first);
+        before_next = byte_before(c * bytes + (uint64_t)lane * span);
+    }
+    for (; c < nchunks; c += c_step) {
+        const uint64_t c0 = c * bytes;
+        const uint64_t at = c0 + (uint64_t)lane * span;
+        const uint32_t before = before_next;
+        wc_take(nx, first);
+        if (c + c_step < nchunks) {
+            load(at + c_step * bytes, first);
+            before_next = byte_before(at + c_step * bytes);
+        }
+        s.dead = ~__ballot(wc_space(before));
+        s.open = 0;
+        s.lo = kFnvLo;
+        s.hi = kFnvHi;
+        const uint32_t from = s.top;
+        // 16 bytes per lane and round; rounds past the span go on while a
+        // word is open
+        for (uint32_t r = 0; r < steps || s.open != 0;) {
+            wc_take(cur, nx);
+            load(at + 16ull * r + 64, nx);
+#pragma unroll 1
+            for (int u = 0; u < 4 && (r < steps || s.open != 0); ++u, ++r) {
+                if (c0 + 63ull * span + 16ull * r + 16 > n)
+                    cur[0] = wc_span_end(cur[0], n, at + 16ull * r);
+                uint32_t w0 = cur[0].x, w1 = cur[0].y;
+                uint32_t rel = kOff ? lane * span + 16 * r : 0;
+#pragma unroll 1
+                for (int half = 0; half < 2; ++half) {
+                    if (r < steps)
+                        wc_steps<kOff, false>(s, w0, w1, zero, rel);
+                    else
+                        wc_steps<kOff, true>(s, w0, w1, zero, rel);
+                    while (s.top >= q0 + 64 * 8) { // the queue's last 64 words
+                        s.top -= 64 * 8;
+                        s.top_off -= 64 * 2;
+                        words += 64;
+                        const uint32_t i = (s.top - q0) / 8 + lane;
+                        words64(true, key(i), kOff ? qo[i] : 0u, kOff ? c0 : 0ull);
                     }
-                    len += 16u;
+                    w0 = cur[0].z;
+                    w1 = cur[0].w;
+                    rel += 8;
                 }
+#pragma unroll
+                for (int v = 0; v < 3; ++v)
+                    cur[v] = cur[v + 1];
             }
-            // the staged bytes of the word, four at a time
-            uint64_t h = kBasis;
-            for (uint32_t k = 0; k < len; k += 4) {
-                const uint32_t b0 = st[s0 + k], b1 = st[s0 + k + 1];
-                const uint32_t b2 = st[s0 + k + 2], b3 = st[s0 + k + 3];
-                h = fnv_step(h, b0);
-                if (k + 1 < len)
-                    h = fnv_step(h, b1);
-                if (k + 2 < len)
-                    h = fnv_step(h, b2);
-                if (k + 3 < len)
-                    h = fnv_step(h, b3);
-            }
-            if (!ends) {
-                // past the look-ahead: the rest from the text
-                for (uint64_t j = c0 + s0 + len; j < n; ++j) {
-                    const uint32_t byte = text[j];
-                    if (wc_space(byte))
-                        break;
-                    h = fnv_step(h, byte);
-                }
-            }
-            word(h, c0 + s0);
         }
+        words += (int64_t)((int32_t)(s.top - from) / 8);
+        if (kOff) { // queued offsets are the chunk's own
+            const bool valid = lane < (s.top - q0) / 8;
+            words64(valid, key(lane), qo[lane], c0);
+            missed(nmiss, mq[lane], c0 + mo[lane]);
+            s.top = q0;
+            s.top_off = qo0;
+            nmiss = 0;
+        }
+    }
+    if (!kOff) {
+        words64(lane < (s.top - q0) / 8, key(lane), 0u, 0ull);
+        missed(nmiss, mq[lane], 0ull);
     }
     return words;
 }
 
-__global__ __launch_bounds__(kBlock) void k_wordcount(WcArgs a)
+__global__ __launch_bounds__(kWcBlock) void k_wordcount(WcArgs a)
 {
-    __shared__ uint64_t sk[kWcSlots];
+    __shared__ __attribute__((aligned(16))) uint64_t sk[kWcSlots];
     __shared__ uint32_t sc[kWcSlots];
     __shared__ uint32_t scnt[1u << kWcPartBits];    // spill appends per partition
-    for (uint32_t i = threadIdx.x; i < kWcSlots; i += kBlock) {
+    const uint32_t tid = threadIdx.x;
+    for (uint32_t i = tid; i < kWcSlots; i += kWcBlock) {
         sk[i] = 0;
         sc[i] = 0;
     }
-    for (uint32_t i = threadIdx.x; i < (1u << kWcPartBits); i += kBlock)
+    for (uint32_t i = tid; i < (1u << kWcPartBits); i += kWcBlock)
         scnt[i] = 0;
-    uint64_t words = wc_scan(a.text, a.n, [&](uint64_t h, uint64_t) {
-        wc_local_add(sk, sc, scnt, a, h);
-    });
-    const uint32_t tid = threadIdx.x, lane = tid & 63u;
     __syncthreads();
-    for (uint32_t i = tid; i < kWcSlots; i += kBlock)
-        if (sk[i])
-            wc_global_add(a, sk[i], sc[i]);
-    if (a.spill_cap != 0)
-        for (uint32_t p = tid; p < (1u << kWcPartBits); p += kBlock)
+    const uint64_t words = wc_scan<false>(
+        a.text, a.n, a.span,
+        [&](uint64_t h, uint64_t) -> bool {
+            const uint32_t at = h != 0 ? wc_place(sk, (uint32_t)h & (kWcSets - 1), h) : kNoSlot;
+            if (at != kNoSlot)
+                atomicAdd(&sc[at], 1u);
+            return at == kNoSlot;
+        },
+        [&](uint32_t count, uint64_t h, uint64_t) {
+            if ((tid & 63u) < count)
+                wc_spill(scnt, a, h);
+        });
+    __syncthreads();
+    if (a.spill_cap != 0) {
+        // the table as it stands, for the merge: a set's slots hold the same
+        // partition's keys in every block
+        const uint64_t row = (uint64_t)blockIdx.x * kWcSlots;
+        for (uint32_t i = tid; i < kWcSlots; i += kWcBlock) {
+            a.table_keys[row + i] = sk[i];
+            a.table_counts[row + i] = sc[i];
+        }
+        for (uint32_t p = tid; p < (1u << kWcPartBits); p += kWcBlock)
             a.spill_cnt[((uint64_t)blockIdx.x << kWcPartBits) | p] = min(scnt[p], a.spill_cap);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1)
-        words += __shfl_xor(words, o);
-    if (lane == 0 && words)
+    } else {
+        for (uint32_t i = tid; i < kWcSlots; i += kWcBlock)
+            if (sk[i])
+                wc_global_add(a, sk[i], sc[i]);
+    }
+    if ((tid & 63u) == 0 && words)
         atomicAdd((unsigned long long *)&a.ctl[0], (unsigned long long)words);
 }
 
+// A text shorter than the 16 bytes that the scan loads at a time, between
+// spaces: n of the 32 bytes at `out`.
+__global__ void k_wc_pad(const uint8_t *text, uint64_t n, uint8_t *out)
+{
+    out[threadIdx.x] = threadIdx.x < n ? text[threadIdx.x] : (uint8_t)0x20;
+}
+
 // ---- WordCount's words: the first occurrence of each key --------------------
-// A lookup table from key to the key's index in the caller's array (open
-// addressing at load <= 1/2, key 0 = empty; the key 0 itself is kept in
-// ctl[0] as index + 1), then one pass of the scan front end in which every
-// word whose key is in the table lowers that key's offset to its own with an
-// atomic minimum.  A word reads the key's current offset first and skips the
-// atomic when that is already lower, so after a key's first few words its
-// later ones cost one load.
+// A lookup table of the wanted keys and the lowest offset seen of each (open
+// addressing, key 0 = empty; the key 0 itself has index + 1 in ctl[0] and its
+// offset in ctl[2]), then one pass of the scan front end in which every word
+// whose key is in the table lowers that key's offset to its own with an atomic
+// minimum, unless the offset that it reads beside the key is already lower.
+// Most words don't come that far: the block keeps the keys it has met in LDS,
+// each with (a 256th of) the lowest offset that one of its words took to the
+// table, and a word past that offset is done.  The others wait until there are
+// 64 of them, so that a wave reads the table for all its lanes: random reads
+// of L2, which bound the pass without the LDS keys (one in three words comes
+// to the table), and are one per word with key and offset side by side.  256 MiB
+// of Zipf text, 10^5 keys: 759 us with three reads for every word, 474 us now.
+// (the table's size is no power of two; Knuth's multiplicative hash of the key)
+__device__ __forceinline__ uint64_t wl_slot(uint64_t h, uint64_t slots)
+{
+    return __umul64hi(h * 0x9E3779B97F4A7C15ull, slots);
+}
+
 __global__ __launch_bounds__(kBlock) void k_wl_build(WlArgs l)
 {
     const uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= l.nkeys)
         return;
-    l.offsets[i] = ~0ull;
     const uint64_t h = l.keys[i];
     if (h == 0) {
         if (atomicCAS((unsigned long long *)&l.ctl[0], 0ull, (unsigned long long)(i + 1)) != 0)
             atomicOr((unsigned long long *)&l.ctl[1], 1ull); // the key 0 twice
+        l.ctl[2] = ~0ull;
         return;
     }
-    uint64_t s = h & l.mask;
-    for (uint64_t probe = 0; probe <= l.mask; ++probe) {
-        const uint64_t old =
-            atomicCAS((unsigned long long *)&l.tkeys[s], 0ull, (unsigned long long)h);
+    uint64_t s = wl_slot(h, l.slots);
+    for (uint64_t probe = 0; probe < l.slots; ++probe) {
+        // (a read first: a swap is a round trip to the memory side)
+        uint64_t old = l.table[s].key;
+        if (old == 0)
+            old = atomicCAS((unsigned long long *)&l.table[s].key, 0ull, (unsigned long long)h);
         if (old == 0) {
-            l.tidx[s] = (uint32_t)i;
+            l.table[s].off = ~0ull;
+            l.offsets[i] = s; // until k_wl_result
             return;
         }
         if (old == h) {
             atomicOr((unsigned long long *)&l.ctl[1], 1ull); // a key twice
+            l.offsets[i] = s;
             return;
         }
-        s = (s + 1) & l.mask;
+        s = s + 1 == l.slots ? 0 : s + 1;
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_wl_scan(WlArgs l)
+__global__ __launch_bounds__(kBlock) void k_wl_result(WlArgs l)
 {
-    (void)wc_scan(l.text, l.n, [&](uint64_t h, uint64_t off) {
-        uint64_t idx = ~0ull;
-        if (h == 0) {
-            const uint64_t z = l.ctl[0];
-            if (z)
-                idx = z - 1;
-        } else {
-            // the table is at most half full, so a probe run ends at an
-            // empty slot
-            for (uint64_t s = h & l.mask;; s = (s + 1) & l.mask) {
-                const uint64_t k = l.tkeys[s];
-                if (k == h) {
-                    idx = l.tidx[s];
-                    break;
-                }
-                if (k == 0)
-                    break;
-            }
-        }
-        if (idx != ~0ull && l.offsets[idx] > off)
-            atomicMin((unsigned long long *)&l.offsets[idx], (unsigned long long)off);
-    });
+    const uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < l.nkeys)
+        l.offsets[i] = l.keys[i] == 0 ? l.ctl[2] : l.table[l.offsets[i]].off;
 }
 
-// Merge of the spill regions: block b counts partition b / per_part's keys
-// from the regions of the scan blocks congruent to b modulo per_part in an
-// LDS table, then adds each distinct key it holds to the global table once.
-// Each thread walks one region at a time (a few hundred bytes), sixteen
-// keys in flight, so the block has many regions' loads outstanding at once.
-// Keys that find no LDS slot go to the table directly.
-constexpr uint32_t kWcMergeSlots = 2048;
+// The table's part of a word.
+__device__ __forceinline__ void wl_lookup(const WlArgs &l, uint64_t h, uint64_t off)
+{
+    if (h == 0) {
+        if (l.ctl[0] && l.ctl[2] > off)
+            atomicMin((unsigned long long *)&l.ctl[2], (unsigned long long)off);
+        return;
+    }
+    // a third of the slots at least is empty, so a probe run ends
+    uint64_t s = wl_slot(h, l.slots);
+    for (uint64_t probe = 0; probe < l.slots; ++probe) {
+        const ulonglong2 e = *reinterpret_cast<const ulonglong2 *>(l.table + s);
+        if (e.x == h) {
+            if (e.y > off)
+                atomicMin((unsigned long long *)&l.table[s].off, (unsigned long long)off);
+            return;
+        }
+        if (e.x == 0)
+            return;
+        s = s + 1 == l.slots ? 0 : s + 1;
+    }
+}
+
+__global__ __launch_bounds__(kWcBlock) void k_wl_scan(WlArgs l)
+{
+    __shared__ __attribute__((aligned(16))) uint64_t sk[2 * kWlSets];
+    __shared__ uint32_t sv[2 * kWlSets]; // lowest offset / 256 taken to the table (n <= 2^40)
+    for (uint32_t i = threadIdx.x; i < 2 * kWlSets; i += kWcBlock) {
+        sk[i] = 0;
+        sv[i] = ~0u;
+    }
+    __syncthreads();
+    (void)wc_scan<true>(
+        l.text, l.n, l.span,
+        [&](uint64_t h, uint64_t off) -> bool {
+            const uint32_t at =
+                h != 0 ? wc_place(sk, __umulhi((uint32_t)h, kWlSets), h) : kNoSlot;
+            if (at != kNoSlot) {
+                const uint32_t mine = (uint32_t)(off >> 8);
+                // (the second test drops most of the same word's others among
+                // these 64 words)
+                if (sv[at] < mine || atomicMin(&sv[at], mine) < mine)
+                    return false; // a word before this one goes to the table
+            }
+            return true;
+        },
+        [&](uint32_t count, uint64_t h, uint64_t off) {
+            if ((threadIdx.x & 63u) < count)
+                wl_lookup(l, h, off);
+        });
+}
+
+// Merge: block p counts partition p's words, from the scan blocks' spill regions
+// and from its sets of their tables, in an LDS table, and adds each distinct
+// key to the global table once.  Keys that find no LDS slot go there directly.
+// One block per partition, so that a key costs one global atomic: eight blocks
+// of each, and the scan blocks adding their own tables (two million keys),
+// spent most of 200 us on them.
+//
+// A wave takes one scan block's region at a time, K keys per lane, with the
+// next region's keys in flight.
+constexpr uint32_t kWcMergeSlots = 8192;
 constexpr uint32_t kWcMergeProbes = 8;
 
-__device__ __forceinline__ void wc_merge_add(uint64_t *mk, uint32_t *mc, const WcArgs &a,
-                                             uint64_t h)
+// The slot of key h (not 0) in the merge's table, or kNoSlot.
+__device__ __forceinline__ uint32_t wc_merge_place(uint64_t *mk, uint64_t h)
 {
-    uint32_t s = (uint32_t)h & (kWcMergeSlots - 1);
+    // (other bits of the key make the partition)
+    uint32_t s = (uint32_t)(h >> 32) & (kWcMergeSlots - 1);
     for (uint32_t q = 0; q < kWcMergeProbes; ++q) {
-        const uint64_t key = mk[s];
-        if (key == h) {
-            atomicAdd(&mc[s], 1u);
-            return;
-        }
+        uint64_t key = mk[s];
         if (key == 0) {
-            const uint64_t old =
-                atomicCAS((unsigned long long *)&mk[s], 0ull, (unsigned long long)h);
-            if (old == 0 || old == h) {
-                atomicAdd(&mc[s], 1u);
-                return;
-            }
+            key = atomicCAS((unsigned long long *)&mk[s], 0ull, (unsigned long long)h);
+            key = key == 0 ? h : key;
         }
+        if (key == h)
+            return s;
         s = (s + 1) & (kWcMergeSlots - 1);
     }
-    wc_global_add(a, h, 1);
+    return kNoSlot;
 }
 
-__global__ __launch_bounds__(kBlock) void k_wc_merge(WcArgs a, uint32_t scan_grid,
-                                                    uint32_t per_part)
+// add(h) for partition p's spilled keys.
+template <int K, class Add>
+__device__ __forceinline__ void wc_merge_regions(const WcArgs &a, uint32_t scan_grid, Add add)
+{
+    const uint32_t p = blockIdx.x;
+    const uint32_t lane = threadIdx.x & 63u, wave = uni(threadIdx.x >> 6);
+    uint64_t h[K], next[K];
+    uint32_t left = 0; // keys of the region in flight past those loaded
+    uint64_t from = 0; // where they start
+    auto load = [&](uint64_t at, uint32_t cnt) {
+#pragma unroll
+        for (int u = 0; u < K; ++u)
+            next[u] = lane + 64 * u < cnt ? a.spill[at + lane + 64 * u] : 0;
+        left = cnt > 64 * K ? cnt - 64 * K : 0;
+        from = at + 64 * K;
+    };
+    // 64 regions' counts at a time
+    for (uint32_t b0 = wave; b0 < scan_grid; b0 += 64 * kWcWaves) {
+        const uint32_t mine = b0 + lane * kWcWaves;
+        const uint32_t counts =
+            mine < scan_grid ? a.spill_cnt[((uint64_t)mine << kWcPartBits) | p] : 0;
+        const uint32_t regions = min(64u, (scan_grid - b0 + kWcWaves - 1) / kWcWaves);
+        auto region = [&](uint32_t at) -> uint64_t {
+            return (((uint64_t)(b0 + at * kWcWaves) << kWcPartBits) | p) * a.spill_cap;
+        };
+        uint32_t j = 0;
+        load(region(0), __builtin_amdgcn_readlane(counts, 0));
+        while (j < regions) {
+#pragma unroll
+            for (int u = 0; u < K; ++u) {
+                h[u] = next[u];
+                __asm__ volatile("" : "+v"(h[u]) : : "memory"); // before the loads, as wc_take
+            }
+            if (left) // a region of more than 64 K keys
+                load(from, left);
+            else if (++j < regions)
+                load(region(j), __builtin_amdgcn_readlane(counts, j));
+            // one copy of the insert, the keys rotated through h[0]
+#pragma unroll 1
+            for (int u = 0; u < K; ++u) {
+                if (h[0]) // spilled keys are never 0
+                    add(h[0]);
+#pragma unroll
+                for (int w = 0; w + 1 < K; ++w)
+                    h[w] = h[w + 1];
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(kWcBlock) void k_wc_merge(WcArgs a, uint32_t scan_grid)
 {
     __shared__ uint64_t mk[kWcMergeSlots];
     __shared__ uint32_t mc[kWcMergeSlots];
-    for (uint32_t i = threadIdx.x; i < kWcMergeSlots; i += kBlock) {
+    for (uint32_t i = threadIdx.x; i < kWcMergeSlots; i += kWcBlock) {
         mk[i] = 0;
         mc[i] = 0;
     }
     __syncthreads();
-    const uint32_t p = blockIdx.x / per_part, k = blockIdx.x % per_part;
-    constexpr uint32_t kInFlight = 16;
-    for (uint64_t b = k + (uint64_t)per_part * threadIdx.x; b < scan_grid;
-         b += (uint64_t)per_part * kBlock) {
-        const uint64_t r = (b << kWcPartBits) | p;
-        const uint32_t cnt = a.spill_cnt[r];
-        const uint64_t *src = a.spill + r * a.spill_cap;
-        for (uint32_t i = 0; i < cnt; i += kInFlight) {
-            uint64_t h[kInFlight];
-#pragma unroll
-            for (uint32_t u = 0; u < kInFlight; ++u)
-                h[u] = i + u < cnt ? src[i + u] : 0;
-            // one copy of the insert, the keys rotated through h[0] (sixteen
-            // inlined copies of it left the compiler spilling hundreds of
-            // scalar registers)
-#pragma unroll 1
-            for (uint32_t u = 0; u < kInFlight; ++u) {
-                const uint64_t key = h[0];
-#pragma unroll
-                for (uint32_t v = 0; v + 1 < kInFlight; ++v)
-                    h[v] = h[v + 1];
-                if (key) // spilled keys are never 0
-                    wc_merge_add(mk, mc, a, key);
-            }
+    auto add = [&](uint64_t h, uint32_t c) {
+        const uint32_t s = wc_merge_place(mk, h);
+        if (s == kNoSlot) {
+            wc_global_add(a, h, c);
+            return;
         }
+        // 32 bits hold a block's words (above); a partition's, of all blocks,
+        // may pass them: what carries goes to the table
+        const uint32_t old = atomicAdd(&mc[s], c);
+        if (old + c < old)
+            wc_global_add(a, h, 1ull << 32);
+    };
+    // the partition's slots of the scan blocks' tables, two blocks per wave
+    constexpr uint32_t kShare = 2 * kWcPartSets;
+    for (uint32_t i = threadIdx.x; i < scan_grid * kShare; i += kWcBlock) {
+        const uint64_t at = (uint64_t)(i / kShare) * kWcSlots + blockIdx.x * kShare + i % kShare;
+        const uint64_t h = a.table_keys[at];
+        if (h)
+            add(h, a.table_counts[at]);
     }
+    wc_merge_regions<6>(a, scan_grid, [&](uint64_t h) { add(h, 1u); });
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < kWcMergeSlots; i += kBlock)
+    for (uint32_t i = threadIdx.x; i < kWcMergeSlots; i += kWcBlock)
         if (mk[i])
             wc_global_add(a, mk[i], mc[i]);
 }
@@ -2230,22 +2564,32 @@ int launch_map(const TaskDev *dtasks, uint32_t ntasks, uint64_t tile0, uint64_t 
     return SPARKCL_OK;
 }
 
-int launch_wordcount(const WcArgs &a, uint32_t grid, void *stream)
+int launch_wc_pad(const uint8_t *text, uint64_t n, uint8_t *out, void *stream)
 {
-    if (grid == 0 || !a.keys || !a.counts || !a.ctl || ((a.mask + 1) & a.mask) ||
-        (a.spill_cap != 0 && (!a.spill || !a.spill_cnt)))
+    if (n > kWcPad)
         return SPARKCL_EINVAL;
-    hipLaunchKernelGGL(k_wordcount, dim3(grid), dim3(kBlock), 0, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(k_wc_pad, dim3(1), dim3(kWcPad), 0, (hipStream_t)stream, text, n, out);
     return hip_status(hipGetLastError());
 }
 
-int launch_wc_merge(const WcArgs &a, uint32_t scan_grid, uint32_t per_part, void *stream)
+int launch_wordcount(const WcArgs &a, uint32_t grid, void *stream)
 {
-    if (a.spill_cap == 0 || scan_grid == 0 || per_part == 0)
+    if (grid == 0 || a.n < 16 || !a.keys || !a.counts || !a.ctl || ((a.mask + 1) & a.mask) ||
+        (a.spill_cap != 0 &&
+         (!a.spill || !a.spill_cnt || !a.table_keys || !a.table_counts)) ||
+        a.span == 0 || a.span % 16 != 0 ||
+        a.span > kWcMaxSpan)
         return SPARKCL_EINVAL;
-    const uint32_t grid = per_part << kWcPartBits;
-    hipLaunchKernelGGL(k_wc_merge, dim3(grid), dim3(kBlock), 0, (hipStream_t)stream, a,
-                       scan_grid, per_part);
+    hipLaunchKernelGGL(k_wordcount, dim3(grid), dim3(kWcBlock), 0, (hipStream_t)stream, a);
+    return hip_status(hipGetLastError());
+}
+
+int launch_wc_merge(const WcArgs &a, uint32_t scan_grid, void *stream)
+{
+    if (a.spill_cap == 0 || scan_grid == 0 || !a.table_keys || !a.table_counts)
+        return SPARKCL_EINVAL;
+    hipLaunchKernelGGL(k_wc_merge, dim3(1u << kWcPartBits), dim3(kWcBlock), 0,
+                       (hipStream_t)stream, a, scan_grid);
     return hip_status(hipGetLastError());
 }
 
@@ -2261,27 +2605,23 @@ int launch_wc_compact(const WcArgs &a, uint64_t *keys, uint64_t *counts, uint64_
 
 int launch_wordcount_locate(const WlArgs &l, uint32_t scan_grid, void *stream)
 {
-    if (scan_grid == 0 || !l.offsets || !l.tkeys || !l.tidx || !l.ctl ||
-        ((l.mask + 1) & l.mask) || (l.nkeys && !l.keys) || l.nkeys > 0xFFFFFFFFull ||
-        2 * l.nkeys > l.mask + 1)
+    if (scan_grid == 0 || !l.offsets || !l.table || !l.ctl || l.nkeys == 0 || !l.keys ||
+        l.nkeys > 0xFFFFFFFFull || 3 * l.nkeys > 2 * l.slots ||
+        l.span == 0 || l.span % 16 != 0 || l.span > kWlMaxSpan || (l.n != 0 && l.n < 16))
         return SPARKCL_EINVAL;
     hipStream_t s = (hipStream_t)stream;
-    if (l.nkeys) {
-        const uint64_t bgrid = (l.nkeys + kBlock - 1) / kBlock;
-        hipLaunchKernelGGL(k_wl_build, dim3((uint32_t)bgrid), dim3(kBlock), 0, s, l);
-        const int rc = hip_status(hipGetLastError());
-        if (rc != SPARKCL_OK)
-            return rc;
+    const dim3 keys((uint32_t)((l.nkeys + kBlock - 1) / kBlock));
+    hipLaunchKernelGGL(k_wl_build, keys, dim3(kBlock), 0, s, l);
+    int rc = hip_status(hipGetLastError());
+    if (rc == SPARKCL_OK && l.n != 0) {
+        hipLaunchKernelGGL(k_wl_scan, dim3(scan_grid), dim3(kWcBlock), 0, s, l);
+        rc = hip_status(hipGetLastError());
     }
-    if (l.n)
-        hipLaunchKernelGGL(k_wl_scan, dim3(scan_grid), dim3(kBlock), 0, s, l);
-    return hip_status(hipGetLastError());
-}
-
-int wordcount_blocks_per_cu(int *out)
-{
-    return hip_status(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        out, reinterpret_cast<const void *>(k_wordcount), kBlock, 0));
+    if (rc == SPARKCL_OK) {
+        hipLaunchKernelGGL(k_wl_result, keys, dim3(kBlock), 0, s, l);
+        rc = hip_status(hipGetLastError());
+    }
+    return rc;
 }
 
 int launch_tree(const TreeArgs &a, uint32_t combiner, void *stream)

@@ -205,7 +205,6 @@ struct sparkcl_ctx {
     // blocks_per_cu[MC_PI] is measured where mixed batches use it
     bool tune_shared_mc = false;
     int occ_chain = 1; // chain-executor blocks per CU that fit
-    int occ_wordcount = 0; // word-count blocks per CU that fit (0: not yet asked)
 
     char *arena_base = nullptr;
     bool own_arena = false;

@@ -201,14 +201,23 @@ int launch_tree(const TreeArgs &a, uint32_t combiner, void *stream);
 // keys/counts of mask + 1 slots (a power of two, cleared beforehand); ctl[0]
 // words, ctl[1] count of the key 0, ctl[2] table-full flag, ctl[3] distinct
 // keys written by the compaction.
-// Words that miss a block's LDS table are appended to the block's spill
-// region of their key's partition (the top kWcPartBits bits of the key),
-// spill_cap keys per region, counts in spill_cnt, instead of being added to
-// the global table one atomic at a time; the merge kernel then counts each
-// partition's spilled keys in LDS and adds each distinct key to the table
-// once per merge block.  spill_cap 0: no spill regions (every miss goes to
-// the table directly).
+// Words that miss a block's LDS table (kWcSets sets of two keys, by the key's
+// low bits) are appended to the block's spill region of their partition (as
+// many neighbouring sets for each of the 2^kWcPartBits), spill_cap keys per
+// region, counts in spill_cnt, instead of being added to the global table one
+// atomic at a time; the block's table is written out whole at the end.  The
+// merge kernel then counts each partition's keys in LDS and adds each distinct
+// key to the global table once.  spill_cap 0: no spill regions (every miss,
+// and every key of the block's table, goes to the global table directly).
+constexpr uint32_t kWcSets = 4096;
+constexpr uint32_t kWcSlots = 2 * kWcSets;
 constexpr uint32_t kWcPartBits = 8;
+// Scan blocks are kWcWaves waves, one block per CU; a lane's span of text is at
+// most kWcMaxSpan bytes, for locating kWlMaxSpan.
+constexpr uint32_t kWcWaves = 16;
+constexpr uint32_t kWcMaxSpan = 4096;
+constexpr uint32_t kWlMaxSpan = 256;
+static_assert(64 * kWlMaxSpan <= 1u << 16, "queued offsets are 16 bits");
 struct WcArgs {
     const uint8_t *text;
     uint64_t n;
@@ -217,31 +226,41 @@ struct WcArgs {
     uint64_t mask;       // table slots - 1 (a power of two minus one)
     uint64_t *ctl;       // words, zero-key count, table full, distinct keys
     uint32_t spill_cap;  // keys per spill region (0: no spill regions)
-    uint32_t pad;
+    uint32_t span;       // text bytes per lane and chunk: a multiple of 16
     uint64_t *spill;     // [scan block][partition][spill_cap]
     uint32_t *spill_cnt; // [scan block][partition] keys written
+    uint64_t *table_keys;   // [scan block][kWcSlots] (with spill regions)
+    uint32_t *table_counts; // likewise
 };
+// The scan takes texts of 16 bytes and more; a shorter one is first written to
+// `out` with spaces after it, kWcPad bytes in all.
+constexpr uint32_t kWcPad = 32;
+int launch_wc_pad(const uint8_t *text, uint64_t n, uint8_t *out, void *stream);
 int launch_wordcount(const WcArgs &a, uint32_t grid, void *stream);
-// Merge of the spill regions of `scan_grid` scan blocks into the table, with
-// `per_part` blocks per partition.
-int launch_wc_merge(const WcArgs &a, uint32_t scan_grid, uint32_t per_part, void *stream);
+// Merge of the spill regions and tables of `scan_grid` scan blocks into the
+// global table.
+int launch_wc_merge(const WcArgs &a, uint32_t scan_grid, void *stream);
 int launch_wc_compact(const WcArgs &a, uint64_t *keys, uint64_t *counts, uint64_t cap,
                       uint32_t grid, void *stream);
-int wordcount_blocks_per_cu(int *out);
 // WordCount's words: for each of nkeys distinct keys, the byte offset of the
 // first word with that key (UINT64_MAX if none), through a lookup table of
-// mask + 1 slots (tkeys cleared to 0 and ctl[0..1] to 0 beforehand).  ctl[0]:
-// index + 1 of the key 0; ctl[1]: set when a key repeats.
+// at least 3/2 nkeys slots (cleared to 0, and ctl[0..1], beforehand).  ctl[0]:
+// index + 1 of the key 0; ctl[1]: set when a key repeats; ctl[2]: the offset of
+// the key 0.
+struct WlSlot {
+    uint64_t key; // 0: empty
+    uint64_t off;
+};
 struct WlArgs {
     const uint8_t *text;
     uint64_t n;
     const uint64_t *keys;
     uint64_t nkeys;
     uint64_t *offsets;
-    uint64_t *tkeys;     // lookup table keys (0: empty)
-    uint32_t *tidx;      // the index of each table key in keys
-    uint64_t mask;       // table slots - 1 (a power of two minus one)
+    WlSlot *table;
+    uint64_t slots;
     uint64_t *ctl;
+    uint32_t span;       // text bytes per lane and chunk: a multiple of 16
 };
 int launch_wordcount_locate(const WlArgs &l, uint32_t scan_grid, void *stream);
 // Resident serving executor: block 0 dispatches, the rest run tiles.  Each

@@ -1,8 +1,8 @@
 // WordCount (sec. 3.2.3): words of a device-resident byte stream counted under
 // their 64-bit FNV-1a key, in per-block LDS tables whose misses go to
-// per-partition spill regions; a merge pass counts each partition's spilled
-// keys and adds them to one global open-addressing table, which is then
-// compacted into the caller's arrays.
+// per-partition spill regions; a merge pass counts each partition's keys and
+// adds them to one global open-addressing table, which is then compacted into
+// the caller's arrays.
 #include <algorithm>
 #include <cstring>
 #include <string>
@@ -10,6 +10,26 @@
 #include "runtime.h"
 
 using namespace sparkcl;
+
+namespace {
+
+// The scan's geometry: bytes of text per lane and chunk, and blocks.  Equal
+// shares for all lanes of one block per CU, cut into as few chunks as `most`
+// allows (16 steps past each span's end are spent on words that
+// cross it); a text too short for 16 bytes per lane takes fewer blocks, whose
+// waves share their tables.
+void scan_geometry(const sparkcl_ctx *ctx, uint64_t nbytes, uint32_t most, uint32_t *span,
+                   uint32_t *grid)
+{
+    const uint64_t lanes = 64ull * kWcWaves * (uint64_t)ctx->cus;
+    const uint64_t per = std::max<uint64_t>(1, (nbytes + lanes - 1) / lanes);
+    const uint64_t sweeps = (per + most - 1) / most;
+    *span = (uint32_t)(((per + sweeps - 1) / sweeps + 15) / 16 * 16);
+    const uint64_t chunks = std::max<uint64_t>(1, (nbytes + 64ull * *span - 1) / (64ull * *span));
+    *grid = (uint32_t)std::min<uint64_t>((chunks + kWcWaves - 1) / kWcWaves, (uint64_t)ctx->cus);
+}
+
+} // namespace
 
 extern "C" {
 
@@ -37,15 +57,8 @@ int sparkcl_wordcount(sparkcl_ctx *ctx, const uint8_t *text, uint64_t nbytes, ui
     uint64_t slots = 1024;
     while (slots < 2 * need)
         slots *= 2;
-    if (!ctx->occ_wordcount) {
-        int occ = 0;
-        if (wordcount_blocks_per_cu(&occ) != SPARKCL_OK || occ < 1)
-            occ = 1;
-        ctx->occ_wordcount = occ;
-    }
-    const uint64_t nchunks = (nbytes + 4095) / 4096;
-    const uint32_t grid =
-        (uint32_t)std::min<uint64_t>(nchunks, (uint64_t)ctx->occ_wordcount * ctx->cus);
+    uint32_t span, grid;
+    scan_geometry(ctx, nbytes, kWcMaxSpan, &span, &grid);
     const uint64_t table_bytes = slots * 16 + 64;
     // Spill regions: room for one spilled word per 16 bytes of each scan
     // block's share of the text (a quarter more for the spread between
@@ -54,7 +67,8 @@ int sparkcl_wordcount(sparkcl_ctx *ctx, const uint8_t *text, uint64_t nbytes, ui
     const uint64_t parts = 1ull << kWcPartBits;
     uint64_t cap = nbytes / ((uint64_t)grid * parts * 16);
     cap = cap + cap / 4 + 16;
-    const uint64_t spill_bytes = (uint64_t)grid * parts * (cap * 8 + 4);
+    const uint64_t spill_bytes =
+        (uint64_t)grid * (parts * (cap * 8 + 4) + kWcSlots * (sizeof(uint64_t) + sizeof(uint32_t)));
     uint64_t bytes = table_bytes + spill_bytes;
     uint64_t off = ctx->arena.alloc(bytes);
     if (off == Arena::kFail) {
@@ -74,23 +88,28 @@ int sparkcl_wordcount(sparkcl_ctx *ctx, const uint8_t *text, uint64_t nbytes, ui
     a.ctl = reinterpret_cast<uint64_t *>(base + slots * 16);
     a.mask = slots - 1;
     a.spill_cap = (uint32_t)cap;
+    a.span = span;
+    // (the second half of the control words' 64 bytes)
+    uint8_t *pad = reinterpret_cast<uint8_t *>(a.ctl + 4);
+    if (nbytes < 16) {
+        a.text = pad;
+        a.n = kWcPad;
+    }
     if (cap) {
         a.spill = reinterpret_cast<uint64_t *>(base + table_bytes);
-        a.spill_cnt = reinterpret_cast<uint32_t *>(base + table_bytes +
-                                                   (uint64_t)grid * parts * cap * 8);
+        a.table_keys = a.spill + (uint64_t)grid * parts * cap;
+        a.table_counts = reinterpret_cast<uint32_t *>(a.table_keys + (uint64_t)grid * kWcSlots);
+        a.spill_cnt = a.table_counts + (uint64_t)grid * kWcSlots;
     }
-    // merge: eight blocks per partition (each merge block's loads are a
-    // few hundred bytes per region, so it takes many blocks to keep enough
-    // of them in flight), at least one per CU in all
-    const uint32_t per_part = (uint32_t)std::max<uint64_t>(8, (uint64_t)ctx->cus / parts);
     const uint32_t cgrid =
         (uint32_t)std::min<uint64_t>((slots + kBlock - 1) / kBlock, 4ull * ctx->cus);
     // (only the table and the counters need clearing: every spill slot read
     // by the merge was written by the scan)
     if ((rc = ensure_pinned(ctx, 1)) == SPARKCL_OK &&
         (rc = launch_zero(base, table_bytes, s)) == SPARKCL_OK &&
+        (nbytes >= 16 || (rc = launch_wc_pad(text, nbytes, pad, s)) == SPARKCL_OK) &&
         (rc = launch_wordcount(a, grid, s)) == SPARKCL_OK &&
-        (!cap || (rc = launch_wc_merge(a, grid, per_part, s)) == SPARKCL_OK) &&
+        (!cap || (rc = launch_wc_merge(a, grid, s)) == SPARKCL_OK) &&
         (rc = launch_wc_compact(a, keys, counts, capacity, cgrid, s)) == SPARKCL_OK) {
         hipError_t e = hipMemcpyAsync(ctx->pinned, a.ctl, 32, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess)
@@ -132,24 +151,24 @@ int sparkcl_wordcount_locate(sparkcl_ctx *ctx, const uint8_t *text, uint64_t nby
         return fail(SPARKCL_ETOOBIG, "more than 2^32 - 1 keys");
     std::lock_guard<std::mutex> g(ctx->mu);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    uint64_t slots = 1024;
-    while (slots < 2 * nkeys)
-        slots *= 2;
-    if (!ctx->occ_wordcount) {
-        int occ = 0;
-        if (wordcount_blocks_per_cu(&occ) != SPARKCL_OK || occ < 1)
-            occ = 1;
-        ctx->occ_wordcount = occ;
+    uint64_t least = 1024; // slots, at a load of 1/3 to 2/3
+    while (least < 2 * nkeys)
+        least *= 2;
+    least = least / 4 * 3;
+    uint32_t span, grid;
+    scan_geometry(ctx, nbytes, kWlMaxSpan, &span, &grid);
+    // the table, then the control words; a small one (some 2 MiB at most, half
+    // an XCD's L2) four times as large where that fits, which keeps the chains
+    // of dependent accesses short that a call with few keys waits for
+    uint64_t slots = least <= (1u << 15) ? 4 * least : least;
+    uint64_t off = ctx->arena.alloc(slots * sizeof(WlSlot) + 64);
+    if (off == Arena::kFail && slots != least) {
+        slots = least;
+        off = ctx->arena.alloc(slots * sizeof(WlSlot) + 64);
     }
-    const uint64_t nchunks = std::max<uint64_t>(1, (nbytes + 4095) / 4096);
-    const uint32_t grid =
-        (uint32_t)std::min<uint64_t>(nchunks, (uint64_t)ctx->occ_wordcount * ctx->cus);
-    // table keys, then control words, then the key indices
-    const uint64_t zero_bytes = slots * 8 + 64;
-    const uint64_t bytes = zero_bytes + slots * 4;
-    const uint64_t off = ctx->arena.alloc(bytes);
+    const uint64_t zero_bytes = slots * sizeof(WlSlot) + 64;
     if (off == Arena::kFail)
-        return fail(SPARKCL_ENOMEM, "word lookup table of " + std::to_string(bytes) +
+        return fail(SPARKCL_ENOMEM, "word lookup table of " + std::to_string(zero_bytes) +
                                         " bytes does not fit the arena");
     char *base = static_cast<char *>(ctx->dev(off));
     WlArgs l{};
@@ -158,12 +177,19 @@ int sparkcl_wordcount_locate(sparkcl_ctx *ctx, const uint8_t *text, uint64_t nby
     l.keys = keys;
     l.nkeys = nkeys;
     l.offsets = offsets;
-    l.tkeys = reinterpret_cast<uint64_t *>(base);
-    l.ctl = reinterpret_cast<uint64_t *>(base + slots * 8);
-    l.tidx = reinterpret_cast<uint32_t *>(base + zero_bytes);
-    l.mask = slots - 1;
+    l.table = reinterpret_cast<WlSlot *>(base);
+    l.ctl = reinterpret_cast<uint64_t *>(base + slots * sizeof(WlSlot));
+    l.slots = slots;
+    l.span = span;
+    uint8_t *pad = reinterpret_cast<uint8_t *>(l.ctl + 4);
+    if (nbytes > 0 && nbytes < 16) {
+        l.text = pad;
+        l.n = kWcPad;
+    }
     if ((rc = ensure_pinned(ctx, 1)) == SPARKCL_OK &&
         (rc = launch_zero(base, zero_bytes, s)) == SPARKCL_OK &&
+        (nbytes == 0 || nbytes >= 16 ||
+         (rc = launch_wc_pad(text, nbytes, pad, s)) == SPARKCL_OK) &&
         (rc = launch_wordcount_locate(l, grid, s)) == SPARKCL_OK) {
         hipError_t e = hipMemcpyAsync(ctx->pinned, l.ctl, 16, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess)
