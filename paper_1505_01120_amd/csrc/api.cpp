@@ -247,6 +247,74 @@ uint32_t sparkcl::exec_grid(const sparkcl_ctx *ctx, uint32_t kid_mask, uint64_t 
     return std::max(1u, waves * (uint32_t)kBlock / block) * (uint32_t)ctx->cus;
 }
 
+namespace {
+
+// Elements of a tile that moves about `bytes`; a power of two.
+uint32_t even_tile(const sparkcl_task &t, uint64_t bytes)
+{
+    return (uint32_t)(bytes / (t.kernel_id == SPARKCL_POLY && !t.out ? 4 : 8));
+}
+
+// The tile size of a batch of streaming tasks too small for the batched
+// table's tiles: the per-launch table is tuned on one task at a time and cuts
+// such a batch into several times as many tiles as blocks, each with its two
+// memory round trips and its queue atomic.  Taken is the size of least
+// estimated time: rounds of tiles, each the time of its bytes and of about
+// 110 KB more (4 us at a block's share of 7 TB/s; a third of that if no task
+// has more than one tile, and so none a ticket); one round alone counts half
+// its bytes again, since the blocks that share a CU with another then finish
+// last with nothing left to even it out.  One block per CU streams best (the
+// caller's count, if it gives one).  Tiles that also write stop at 512 KB:
+// 20 tasks of 3e6 elements took 133 us so and 138 at 1 MB.
+// Measured on MI355X, per-launch table and this rule: 64 FMUL tasks of 2^20
+// elements 125 and 90 us, as a chain of three maps 179 and 126; 48 POLY tasks
+// of 300007 41 and 33 (with their values written 44 and 41); 256 of 20001 29
+// and 22; 16 of 10^6 with values 56 and 39.  Batches with Monte-Carlo tasks,
+// which compute, stay with the table, and so do tables that the caller set.
+void even_cut(const sparkcl_ctx *ctx, const sparkcl_task *tasks, uint32_t ntasks, uint32_t mask,
+              uint32_t per_cu, sparkcl::Cut *c)
+{
+    if (mask & (1u << (SPARKCL_MC_PI - 1)))
+        return;
+    if (per_cu == 0)
+        per_cu = ctx->config.exec_blocks_per_cu ? ctx->config.exec_blocks_per_cu : 1;
+    const uint64_t grid = (uint64_t)per_cu * ctx->cus;
+    const double fixed = 110e3 / per_cu;
+    bool writes = false;
+    uint64_t table_tiles = 0; // of the per-launch table
+    for (uint32_t i = 0; i < ntasks; ++i) {
+        writes |= tasks[i].out != nullptr;
+        const uint32_t T = tile_for(ctx->tuning, TM_PER_LAUNCH, tasks[i].kernel_id, tasks[i].n);
+        table_tiles += std::max<uint64_t>(1, (tasks[i].n + T - 1) / T);
+    }
+    double best = 0;
+    for (uint64_t bytes = 32u << 10; bytes <= (writes ? 512u : 2048u) << 10; bytes *= 2) {
+        uint64_t tiles = 0, largest = 0;
+        bool tickets = false;
+        for (uint32_t i = 0; i < ntasks; ++i) {
+            const uint64_t T = even_tile(tasks[i], bytes);
+            tickets |= tasks[i].n > T;
+            tiles += std::max<uint64_t>(1, (tasks[i].n + T - 1) / T);
+            largest = std::max(largest, std::min(T, tasks[i].n) *
+                                            (input_bytes(tasks[i].kernel_id) +
+                                             (tasks[i].out ? 4 : 0)));
+        }
+        if (tiles > std::max<uint64_t>(table_tiles, 4 * grid))
+            continue; // no more workspace than the table's cut, or little
+        const uint64_t rounds = (tiles + grid - 1) / grid;
+        const double cost = (rounds == 1 ? 1.5 : (double)rounds) * (double)largest +
+                            (double)rounds * (tickets ? fixed : fixed / 3);
+        if (best == 0 || cost < best) {
+            best = cost;
+            c->even_bytes = bytes;
+        }
+    }
+    if (c->even_bytes)
+        c->per_cu = per_cu;
+}
+
+} // namespace
+
 sparkcl::Cut sparkcl::plan_cut(const sparkcl_ctx *ctx, int mode, const sparkcl_task *tasks,
                                 uint32_t ntasks, bool host_in, uint32_t per_cu)
 {
@@ -254,9 +322,10 @@ sparkcl::Cut sparkcl::plan_cut(const sparkcl_ctx *ctx, int mode, const sparkcl_t
     // executor's blocks fewer than two tiles each (a batch of one or a few
     // partitions, where the batched table's large tiles would leave most of
     // the GPU idle, or about one large tile per block, where the time is set
-    // by how unevenly the blocks land on the CUs); such a batch is cut with
-    // the per-launch table instead.  The choice is a function of the call,
-    // so a repeated call is cut the same way.
+    // by how unevenly the blocks land on the CUs); such a batch is cut by
+    // estimated time if it streams, else with the per-launch table.  The
+    // choice is a function of the call, so a repeated call is cut the same
+    // way.
     Cut c;
     c.tm = mode != SPARKCL_PER_LAUNCH && !host_in ? TM_BATCHED : TM_PER_LAUNCH;
     // A batch of many tasks of widely spread sizes takes the mixed-batch
@@ -313,6 +382,8 @@ sparkcl::Cut sparkcl::plan_cut(const sparkcl_ctx *ctx, int mode, const sparkcl_t
             c.tm = TM_PER_LAUNCH;
             c.mixed = false;
             c.share_tile[0] = c.share_tile[1] = c.share_tile[2] = 0;
+            if (!ctx->own_tuning)
+                even_cut(ctx, tasks, ntasks, mask, per_cu, &c);
         }
     }
     return c;
@@ -320,6 +391,8 @@ sparkcl::Cut sparkcl::plan_cut(const sparkcl_ctx *ctx, int mode, const sparkcl_t
 
 uint32_t sparkcl::cut_tile(const sparkcl_ctx *ctx, const Cut &c, const sparkcl_task &t)
 {
+    if (c.even_bytes)
+        return even_tile(t, c.even_bytes);
     if (c.tm == TM_BATCHED && c.mixed && t.kernel_id >= SPARKCL_POLY &&
         t.kernel_id <= SPARKCL_MC_PI) {
         if (ctx->tuning.tile_many[t.kernel_id - 1])
@@ -573,6 +646,8 @@ int sparkcl::build_plan(sparkcl_ctx *ctx, int kind, int mode, const sparkcl_task
         // map chains run 256-thread blocks; a given per_cu (chains) counts them
         p->block = kind == 4 ? (uint32_t)kBlock : exec_block(ctx, kid_mask);
         p->mc_only = mc_instance(ctx, kid_mask);
+        if (cut.per_cu)
+            per_cu = cut.per_cu;
         p->grid = std::min(per_cu ? per_cu * (uint32_t)ctx->cus
                                   : exec_grid(ctx, kid_mask, p->ntiles_total, ntasks, p->block),
                            p->ntiles_total);
@@ -1257,6 +1332,7 @@ int sparkcl_set_tuning(sparkcl_ctx *ctx, const sparkcl_tuning *in)
     std::lock_guard<std::mutex> g(ctx->mu);
     drop_plans(ctx);
     ctx->tuning = *in;
+    ctx->own_tuning = true;
     if (ctx->server)
         ctx->server->set_tuning(*in);
     return SPARKCL_OK;

@@ -178,6 +178,7 @@ extern "C" int sparkcl_autotune(sparkcl_ctx *ctx, uint32_t lo_log2, uint32_t hi_
     }
 
     sparkcl_tuning best = ctx->tuning;
+    ctx->own_tuning = true; // candidates are measured as the tables say
     const bool verbose = std::getenv("SPARKCL_AUTOTUNE_LOG") != nullptr;
     // Times `tasks` under tuning `t`; false (with rc set) on failure.
     auto measure = [&](const sparkcl_tuning &t, int mode,

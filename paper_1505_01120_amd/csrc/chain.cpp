@@ -67,9 +67,9 @@ int sparkcl_reduce_chain(sparkcl_ctx *ctx, const sparkcl_task *tasks, uint32_t n
         // 4 loads at 4 blocks per CU (407-411 us; with 8 loads 526-558 at 3,
         // where the deeper stream's registers cap the waves).  A grid that
         // would get fewer than two of the batched table's tiles per block
-        // takes the per-launch table's smaller tiles, so blocks keep pulling
-        // tiles from the queue (with one large tile per block, blocks placed
-        // unevenly on the CUs decide the time: 440-490 us at 2 per CU).
+        // is cut smaller (plan_cut), so blocks keep pulling tiles from the
+        // queue (with one large tile per block, blocks placed unevenly on the
+        // CUs decide the time: 440-490 us at 2 per CU).
         uint32_t steps = 0;
         for (uint32_t s = 0; s < nstages; ++s)
             steps += chain.deg[s];

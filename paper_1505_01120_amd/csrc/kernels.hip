@@ -909,28 +909,26 @@ __global__ __launch_bounds__(kMaxBlock) void k_task(const TaskDev *__restrict__ 
             rdd_step(L);
 }
 
-// Persistent executor: a fixed grid of blocks takes tiles from the queue with
-// one atomic each until the queue is empty; thread 0 asks for the next tile
-// while the current one streams, so the queue round trip is hidden.  The last
-// block to leave resets the queue head, so the next launch of the same plan
-// needs no clearing.
+// Persistent executor: a fixed grid of blocks; block b starts with tile b of
+// the queue and takes the others with one atomic each until the queue is
+// empty; thread 0 asks for the next tile while the current one streams, so the
+// queue round trip is hidden.  (All blocks' atomics meet on one address, about
+// 60 a microsecond: 16384 tiles of 4096 elements took 255 us whatever they
+// hold, so tiles of a small call are cut larger than that.)  The last block to
+// leave resets the queue head, so the next launch of the same plan needs no
+// clearing.
 template <class Tile>
 __device__ __forceinline__ void executor(const TaskDev *__restrict__ tasks,
                                          const TileRef *__restrict__ tiles, uint32_t ntiles,
                                          const LaunchOut &L, Tile tile)
 {
     __shared__ uint32_t sh_tile;
-    if (threadIdx.x == 0)
-        sh_tile = __hip_atomic_fetch_add(&L.ctl->head, 1u, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    uint32_t t = uni(sh_tile);
-    __syncthreads();
+    uint32_t t = blockIdx.x;
     while (t < ntiles) {
         uint32_t next = 0;
         if (threadIdx.x == 0)
-            next = __hip_atomic_fetch_add(&L.ctl->head, 1u, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
+            next = gridDim.x + __hip_atomic_fetch_add(&L.ctl->head, 1u, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT);
         const TileRef tr = tiles[t];
         const TaskDev *tp = tasks + uni(tr.task);
         tile(tp, uni(tr.tile));

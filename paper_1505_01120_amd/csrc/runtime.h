@@ -51,6 +51,10 @@ struct Cut {
     // mixed batches: each kernel's tile derived from the batch's totals and
     // the tuned tiles per CU (index kernel id - 1; 0: none derived)
     uint32_t share_tile[3] = {0, 0, 0};
+    // small streaming batches: tiles of this many bytes, on per_cu executor
+    // blocks per CU (0: by the table)
+    uint64_t even_bytes = 0;
+    uint32_t per_cu = 0;
 };
 
 // A cached, uploaded launch: device task table, tile queue, partials, sync
@@ -211,6 +215,7 @@ struct sparkcl_ctx {
     sparkcl::Arena arena;
 
     sparkcl_tuning tuning{};
+    bool own_tuning = false; // set by the caller: its tile tables are taken as they are
     sparkcl_config config{};
 
     std::mutex mu; // plans, events, pinned buffers
