@@ -732,7 +732,7 @@ int sparkcl::ensure_pinned(sparkcl_ctx *ctx, uint32_t count)
     ctx->pinned = nullptr;
     ctx->pinned_cap = 0;
     SPARKCL_HIP(hipHostMalloc((void **)&ctx->pinned, sizeof(sparkcl_result) * cap,
-                              hipHostMallocDefault));
+                              hipHostMallocMapped | hipHostMallocCoherent));
     ctx->pinned_cap = cap;
     return SPARKCL_OK;
 }
@@ -908,12 +908,22 @@ int sparkcl::launch_and_collect(sparkcl_ctx *ctx, Plan *p, const sparkcl_task *t
     int rc;
     if ((rc = ensure_pinned(ctx, ntasks + 1)) != SPARKCL_OK)
         return rc;
-    if ((rc = enqueue(ctx, p, stream, true)) != SPARKCL_OK)
+    // The launch that folds the RDD total writes the per-task results and it
+    // to the pinned buffer; a replayed graph, whose arguments are those of its
+    // capture, and a call of many tasks bring them back in one copy.
+    const bool direct = p->mode != SPARKCL_GRAPH && ntasks <= kHostResults;
+    void *host = nullptr;
+    if (direct)
+        SPARKCL_HIP(hipHostGetDevicePointer(&host, ctx->pinned, 0));
+    p->out.host = static_cast<sparkcl_result *>(host);
+    rc = enqueue(ctx, p, stream, true);
+    p->out.host = nullptr;
+    if (rc != SPARKCL_OK)
         return rc;
-    // the per-task results and the RDD total behind them, in one copy
-    SPARKCL_HIP(hipMemcpyAsync(ctx->pinned, p->dresults,
-                               sizeof(sparkcl_result) * ((uint64_t)ntasks + 1),
-                               hipMemcpyDeviceToHost, stream));
+    if (!direct)
+        SPARKCL_HIP(hipMemcpyAsync(ctx->pinned, p->dresults,
+                                   sizeof(sparkcl_result) * ((uint64_t)ntasks + 1),
+                                   hipMemcpyDeviceToHost, stream));
     SPARKCL_HIP(hipStreamSynchronize(stream));
     if (per_task)
         std::memcpy(per_task, ctx->pinned, sizeof(sparkcl_result) * ntasks);

@@ -737,6 +737,22 @@ __device__ __forceinline__ void rdd_total(const LaunchOut &L)
         own_stores_complete();
     }
     __syncthreads();
+    if (L.host) {
+        // A blocking call: its results go to the host from here, 64 bytes a
+        // task over the link, instead of by a copy after the launch, which
+        // waited for it, took as long again and was waited for (one task of
+        // 1000 elements, whole call: 29.1 us with the copy, 22.6 without).
+        constexpr uint32_t kWords = sizeof(sparkcl_result) / 8;
+        uint64_t *to = reinterpret_cast<uint64_t *>(L.host);
+        const uint64_t *res = reinterpret_cast<const uint64_t *>(L.results);
+        const uint64_t *tot = reinterpret_cast<const uint64_t *>(L.total);
+        const uint32_t n = L.ntasks * kWords;
+        for (uint32_t i = threadIdx.x; i < n + kWords; i += blockDim.x)
+            __hip_atomic_store(to + i, ld_agent(i < n ? res + i : tot + (i - n)),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        own_stores_complete();
+        __syncthreads();
+    }
 }
 
 // RDD-level step of the per-partition launches, run by the block that

@@ -74,6 +74,10 @@ struct TaskSync {
 };
 static_assert(sizeof(TaskSync) == 16, "TaskSync layout");
 
+// Tasks of a blocking call whose results the launch itself writes to the host;
+// larger calls copy them.
+constexpr uint32_t kHostResults = 1024;
+
 // Persistent-executor queue state; every field returns to zero at kernel end
 // so the next launch needs no clearing.
 struct BatchCtl {
@@ -94,6 +98,8 @@ struct LaunchOut {
     BatchCtl *ctl;
     sparkcl_result *results; // per task index, contiguous
     sparkcl_result *total;   // RDD-level total, or nullptr
+    sparkcl_result *host;    // host-coherent copies of both (ntasks results, then the
+                             // total) written with the total, or nullptr
     uint64_t *done;          // serving: completion words (seq + 1), or nullptr
     uint32_t ntasks;         // tasks in the RDD-level combine (0: none)
     uint32_t ns_per_tick;    // device wall clock period
