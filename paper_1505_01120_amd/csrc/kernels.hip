@@ -1441,11 +1441,21 @@ __global__ __launch_bounds__(BT) void k_tree_wide(TreeArgs a)
             TreeVec<4>::st(o + col[c], acc[c], skip[c]);
 }
 
+// (16 bytes per store from the first 16-byte boundary on: 16 MiB in 8.2 us, in
+// single words 9.2.)
 __global__ __launch_bounds__(kBlock) void k_zero(uint32_t *p, uint64_t words)
 {
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
-    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < words; i += stride)
-        p[i] = 0u;
+    const uint64_t at = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+    const uint64_t head = min((uint64_t)((0u - (uint32_t)((uintptr_t)p >> 2)) & 3u), words);
+    const uint64_t quads = (words - head) / 4, tail = head + 4 * quads;
+    uint4 *q = reinterpret_cast<uint4 *>(p + head);
+    for (uint64_t i = at; i < quads; i += stride)
+        q[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (at < head)
+        p[at] = 0u;
+    if (at < words - tail)
+        p[tail + at] = 0u;
 }
 
 // ---- WordCount --------------------------------------------------------------
@@ -1480,6 +1490,7 @@ __global__ __launch_bounds__(kBlock) void k_zero(uint32_t *p, uint64_t words)
 constexpr int kWcBlock = (int)kWcWaves * 64;
 constexpr uint32_t kWcQueue = 64 + 4 * 64; // a wave's waiting words: 8 steps end
                                            // at most 4 per lane
+constexpr uint32_t kWcCompact = 4 * kWcBlock; // table slots of a compaction block
 constexpr uint32_t kWcMissed = 2 * 64;     // those that found no place in the table
 constexpr uint32_t kWcPartSets = kWcSets >> kWcPartBits;
 // Locating keeps offsets beside the words, so its table is smaller.
@@ -2238,63 +2249,53 @@ __global__ __launch_bounds__(kWcBlock) void k_wc_merge(WcArgs a, uint32_t scan_g
 
 // Compaction of the global table into the caller's key/count arrays
 // (unordered); ctl[3] counts the distinct keys, also those past `cap`.  Each
-// block owns a contiguous range of slots: it counts its keys, reserves room
-// with one atomic add (a counter bumped once per key would serialise on
-// that one address), then writes its keys in slot order at its offset.
-__global__ __launch_bounds__(kBlock) void k_wc_compact(WcArgs a, uint64_t *out_keys,
-                                                      uint64_t *out_counts, uint64_t cap)
+// block holds its slots' keys in registers, counts them, reserves room with
+// one atomic add (a counter bumped once per key would serialise on that one
+// address) and writes them there.  Blocks are large for the same reason: 1024
+// blocks' adds of a table of 2^20 slots took most of 20 us, 256 take 9.
+__global__ __launch_bounds__(kWcBlock) void k_wc_compact(WcArgs a, uint64_t *out_keys,
+                                                         uint64_t *out_counts, uint64_t cap)
 {
-    __shared__ uint32_t sh_wave[kWaves];
+    __shared__ uint32_t sh_wave[kWcWaves];
     __shared__ uint64_t sh_base;
-    const uint64_t slots = a.mask + 1;
-    const uint64_t per = (slots + gridDim.x - 1) / gridDim.x;
-    const uint64_t lo = min(slots, (uint64_t)blockIdx.x * per);
-    const uint64_t hi = min(slots, lo + per);
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    // pass 1: this block's key count
-    uint32_t mine = 0;
-    for (uint64_t s = lo + threadIdx.x; s < hi; s += kBlock)
-        mine += a.keys[s] != 0;
+    const uint64_t first = (uint64_t)blockIdx.x * kWcCompact + threadIdx.x;
+    uint64_t k[kWcCompact / kWcBlock];
+    uint32_t mine = 0; // the wave's keys
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1)
-        mine += __shfl_xor(mine, o);
+    for (uint32_t u = 0; u < kWcCompact / kWcBlock; ++u) {
+        const uint64_t s = first + u * kWcBlock;
+        k[u] = s <= a.mask ? a.keys[s] : 0;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kWcCompact / kWcBlock; ++u)
+        mine += (uint32_t)__popcll(__ballot(k[u] != 0));
     if (lane == 0)
         sh_wave[wave] = mine;
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t total = 0;
-        for (int w = 0; w < kWaves; ++w)
-            total += sh_wave[w];
+        for (uint32_t w = 0; w < kWcWaves; ++w) {
+            const uint32_t n = sh_wave[w];
+            sh_wave[w] = total;
+            total += n;
+        }
         sh_base = total ? atomicAdd((unsigned long long *)&a.ctl[3], (unsigned long long)total)
                         : 0;
     }
     __syncthreads();
-    // pass 2: keys in slot order, kBlock slots at a time, placed by a block
-    // prefix sum of the occupied slots
-    uint64_t base = sh_base;
-    __syncthreads();
-    for (uint64_t s0 = lo; s0 < hi; s0 += kBlock) {
-        const uint64_t s = s0 + threadIdx.x;
-        const uint64_t k = s < hi ? a.keys[s] : 0;
-        const uint64_t ballot = __ballot(k != 0);
-        const uint32_t before = __popcll(ballot & ((1ull << lane) - 1));
-        if (lane == 0)
-            sh_wave[wave] = __popcll(ballot);
-        __syncthreads();
-        uint32_t off = 0, total = 0;
-        for (int w = 0; w < kWaves; ++w) {
-            off += w < (int)wave ? sh_wave[w] : 0;
-            total += sh_wave[w];
-        }
-        if (k != 0) {
-            const uint64_t pos = base + off + before;
+    uint64_t base = sh_base + sh_wave[wave];
+#pragma unroll
+    for (uint32_t u = 0; u < kWcCompact / kWcBlock; ++u) {
+        const uint64_t set = __ballot(k[u] != 0);
+        if (k[u] != 0) {
+            const uint64_t pos = base + __popcll(set & ((1ull << lane) - 1));
             if (pos < cap) {
-                out_keys[pos] = k;
-                out_counts[pos] = a.counts[s];
+                out_keys[pos] = k[u];
+                out_counts[pos] = a.counts[first + u * kWcBlock];
             }
         }
-        base += total;
-        __syncthreads();
+        base += __popcll(set);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0 && a.ctl[1]) {
         const uint64_t pos = atomicAdd((unsigned long long *)&a.ctl[3], 1ull);
@@ -2608,12 +2609,13 @@ int launch_wc_merge(const WcArgs &a, uint32_t scan_grid, void *stream)
 }
 
 int launch_wc_compact(const WcArgs &a, uint64_t *keys, uint64_t *counts, uint64_t cap,
-                      uint32_t grid, void *stream)
+                      void *stream)
 {
-    if (grid == 0)
+    const uint64_t grid = (a.mask + kWcCompact) / kWcCompact;
+    if (grid > 0x7fffffffull)
         return SPARKCL_EINVAL;
-    hipLaunchKernelGGL(k_wc_compact, dim3(grid), dim3(kBlock), 0, (hipStream_t)stream, a,
-                       keys, counts, cap);
+    hipLaunchKernelGGL(k_wc_compact, dim3((uint32_t)grid), dim3(kWcBlock), 0,
+                       (hipStream_t)stream, a, keys, counts, cap);
     return hip_status(hipGetLastError());
 }
 
@@ -2721,7 +2723,7 @@ int launch_zero(void *p, uint64_t bytes, void *stream)
     const uint64_t words = bytes / 4;
     if (words == 0)
         return SPARKCL_OK;
-    uint64_t grid = (words + kBlock - 1) / kBlock;
+    uint64_t grid = (words / 4 + kBlock) / kBlock;
     if (grid > 4096)
         grid = 4096;
     hipLaunchKernelGGL(k_zero, dim3((uint32_t)grid), dim3(kBlock), 0,

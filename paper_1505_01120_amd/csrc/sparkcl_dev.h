@@ -247,7 +247,7 @@ int launch_wordcount(const WcArgs &a, uint32_t grid, void *stream);
 // global table.
 int launch_wc_merge(const WcArgs &a, uint32_t scan_grid, void *stream);
 int launch_wc_compact(const WcArgs &a, uint64_t *keys, uint64_t *counts, uint64_t cap,
-                      uint32_t grid, void *stream);
+                      void *stream);
 // WordCount's words: for each of nkeys distinct keys, the byte offset of the
 // first word with that key (UINT64_MAX if none), through a lookup table of
 // at least 3/2 nkeys slots (cleared to 0, and ctl[0..1], beforehand).  ctl[0]:

@@ -101,8 +101,6 @@ int sparkcl_wordcount(sparkcl_ctx *ctx, const uint8_t *text, uint64_t nbytes, ui
         a.table_counts = reinterpret_cast<uint32_t *>(a.table_keys + (uint64_t)grid * kWcSlots);
         a.spill_cnt = a.table_counts + (uint64_t)grid * kWcSlots;
     }
-    const uint32_t cgrid =
-        (uint32_t)std::min<uint64_t>((slots + kBlock - 1) / kBlock, 4ull * ctx->cus);
     // (only the table and the counters need clearing: every spill slot read
     // by the merge was written by the scan)
     if ((rc = ensure_pinned(ctx, 1)) == SPARKCL_OK &&
@@ -110,7 +108,7 @@ int sparkcl_wordcount(sparkcl_ctx *ctx, const uint8_t *text, uint64_t nbytes, ui
         (nbytes >= 16 || (rc = launch_wc_pad(text, nbytes, pad, s)) == SPARKCL_OK) &&
         (rc = launch_wordcount(a, grid, s)) == SPARKCL_OK &&
         (!cap || (rc = launch_wc_merge(a, grid, s)) == SPARKCL_OK) &&
-        (rc = launch_wc_compact(a, keys, counts, capacity, cgrid, s)) == SPARKCL_OK) {
+        (rc = launch_wc_compact(a, keys, counts, capacity, s)) == SPARKCL_OK) {
         hipError_t e = hipMemcpyAsync(ctx->pinned, a.ctl, 32, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess)
             e = hipStreamSynchronize(s);
