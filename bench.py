@@ -589,10 +589,10 @@ def bench_wordcount(ctx, sc, reps=5) -> dict:
             "locate": {"ms": loc_sec * 1e3, "GBps": nbytes / loc_sec / 1e9, "keys": nd,
                        "matches_oracle": loc_exact,
                        "what": "first byte offset of each distinct key's word"},
-            # the scan kernel issues about 0.5 VALU, 0.5 SALU and 0.06 LDS
-            # wave-instructions per text byte and inserts into an LDS hash
-            # table: it is bound by instruction issue and LDS latency, not
-            # by HBM (counters in the WordCount profile summary)
+            # the scan kernel issues about 0.29 VALU, 0.19 SALU and 0.025 LDS
+            # wave-instructions per text byte, the VALU 68% of its cycles: it
+            # is bound by instruction issue, not by HBM (counters in the
+            # WordCount profile summary)
             "bound": {"kind": "issue (VALU, SALU, LDS table inserts)",
                       "hbm_frac": nbytes / sec / 1e9 / HBM_PEAK_GBS,
                       "summary": "profiles/k_wordcount_1gib_counters.md"},
