@@ -154,7 +154,14 @@ int sparkcl_wordcount_locate(sparkcl_ctx *ctx, const uint8_t *text, uint64_t nby
         least *= 2;
     least = least / 4 * 3;
     uint32_t span, grid;
-    scan_geometry(ctx, nbytes, kWlMaxSpan, &span, &grid);
+    // A block's LDS keys settle a word only once one before it has been met, so
+    // the spans of a first chunk, which the waves walk side by side, gain
+    // little by them: shorter ones while there would be fewer than four chunks
+    // (100 MiB: 246 us in two of 192 bytes, 226 in three of 128; 256 MiB: 463 in
+    // four of 256, 467 in eight of 128).
+    const uint64_t lanes = 64ull * kWcWaves * (uint64_t)ctx->cus;
+    scan_geometry(ctx, nbytes, nbytes < 4 * kWlMaxSpan * lanes ? kWlMaxSpan / 2 : kWlMaxSpan,
+                  &span, &grid);
     // the table, then the control words; a small one (some 2 MiB at most, half
     // an XCD's L2) four times as large where that fits, which keeps the chains
     // of dependent accesses short that a call with few keys waits for
