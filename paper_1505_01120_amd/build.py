@@ -3,7 +3,7 @@
 Produces, next to this file:
   libsparkcl.so       -- the C-ABI library (HIP kernels + host runtime), built
                          with hipcc --offload-arch=gfx950;
-  libsparkcl_host.so  -- the pure host logic (arena, admission, tuning cache)
+  libsparkcl_host.so  -- the pure host logic (arena, admission, cuts, tuning cache)
                          behind a small C shim, built with g++, for CPU tests;
   libsparkcl_loadgen.so -- an open-loop serving load generator over the public
                          C ABI (submit / poll at scheduled arrival times), for
@@ -50,8 +50,8 @@ KERNELS = ("k_task", "k_batch", "k_serve", "k_map", "k_chain", "k_tree", "k_tree
 ARCH = "gfx950"
 
 HIP_SOURCES = ["kernels.hip", "noalloc.hip", "api.cpp", "arrays.cpp", "chain.cpp", "wordcount.cpp", "serve.cpp",
-               "autotune.cpp", "tuning.cpp"]
-HOST_SOURCES = ["tuning.cpp", "hostlogic_capi.cpp"]
+               "autotune.cpp", "cut.cpp", "tuning.cpp"]
+HOST_SOURCES = ["cut.cpp", "tuning.cpp", "hostlogic_capi.cpp"]
 
 COMMON = ["-std=c++17", "-O3", "-fPIC", "-fvisibility=hidden", "-Wall", "-Wextra", "-Wno-unused-parameter",
           "-I", INCLUDE, "-I", CSRC]

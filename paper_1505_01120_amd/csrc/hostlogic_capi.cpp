@@ -1,13 +1,15 @@
 // C shim over the pure host logic (arena allocator, map-call overlap check,
-// serving admission control, tuning table and its JSON cache) so it can be unit-tested on a machine
-// without a GPU.  Built with g++ into libsparkcl_host.so; it is not part of
-// the product library's ABI.
+// the cut of a call into tiles, serving admission control, tuning table and
+// its JSON cache) so it can be unit-tested on a machine without a GPU.  Built
+// with g++ into libsparkcl_host.so; it is not part of the product library's
+// ABI.
 #include <cstring>
 #include <map>
 #include <string>
 
 #include "admission.h"
 #include "arena.h"
+#include "cut.h"
 #include "overlap.h"
 #include "tuning.h"
 
@@ -44,6 +46,24 @@ uint64_t hl_arena_size(void *a) { return static_cast<Arena *>(a)->size(); }
 int hl_tasks_independent(const sparkcl_task *tasks, uint32_t ntasks)
 {
     return tasks_independent(tasks, ntasks) ? 1 : 0;
+}
+
+// The cut of a call on a device of `cus` CUs that fit `occ` executor blocks
+// each: 1 if it is cut by estimated time, else 0; each task's tile size in
+// tile[] (0 for an unknown kernel id).
+int hl_cut(const sparkcl_tuning *t, uint32_t cus, uint32_t occ, int mode,
+           const sparkcl_task *tasks, uint32_t ntasks, uint32_t per_cu, uint32_t *tile)
+{
+    ExecEnv env;
+    env.cus = (int)cus;
+    env.occ_batch = env.occ_mc = (int)occ;
+    env.tuning = *t;
+    const Cut c = plan_cut(&env, mode, tasks, ntasks, false, per_cu);
+    for (uint32_t i = 0; i < ntasks; ++i)
+        tile[i] = tasks[i].kernel_id >= SPARKCL_POLY && tasks[i].kernel_id <= SPARKCL_MC_PI
+                      ? cut_tile(&env, c, tasks[i])
+                      : 0;
+    return c.even_bytes != 0;
 }
 
 void *hl_adm_new(uint64_t budget, uint32_t slots, uint64_t tile_cap)

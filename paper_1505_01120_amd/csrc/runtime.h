@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "arena.h"
+#include "cut.h"
 #include "sparkcl.h"
 #include "sparkcl_dev.h"
 #include "tuning.h"
@@ -34,28 +35,12 @@ int check_task(const sparkcl_task &t, uint32_t *variant);
 // Selective execution: a task's offload cost in bytes, and whether the
 // context's threshold declines it.
 uint64_t offload_cost(const sparkcl_task &t);
-// Input bytes a streaming kernel reads per element (x, and y for FMUL).
-uint64_t input_bytes(uint32_t kernel_id);
 bool declined(const sparkcl_ctx *ctx, const sparkcl_task &t);
 
 // Host steady-clock time in ns.
 uint64_t host_ns();
 
 class Server;
-
-// How a reduce-kind call is cut into tiles: the tuning table's row (batched
-// or per-launch) and whether the mixed-batch tile sizes apply.
-struct Cut {
-    int tm = TM_PER_LAUNCH;
-    bool mixed = false;
-    // mixed batches: each kernel's tile derived from the batch's totals and
-    // the tuned tiles per CU (index kernel id - 1; 0: none derived)
-    uint32_t share_tile[3] = {0, 0, 0};
-    // small streaming batches: tiles of this many bytes, on per_cu executor
-    // blocks per CU (0: by the table)
-    uint64_t even_bytes = 0;
-    uint32_t per_cu = 0;
-};
 
 // A cached, uploaded launch: device task table, tile queue, partials, sync
 // words and results.
@@ -125,10 +110,6 @@ struct Plan {
 
 // Plan cache and launch helpers (api.cpp); the caller holds ctx->mu.
 constexpr uint32_t kMaxPlans = 32;     // cached plans per context
-// A batched call is "mixed" (takes sparkcl_tuning.tile_many) with at least
-// this many tasks whose sizes span at least this many log2 buckets.
-constexpr uint32_t kMixedMinTasks = 512;
-constexpr uint32_t kMixedMinSpan = 4;
 constexpr uint64_t kMaxN = 1ull << 40; // elements (or samples, bytes) per task
 
 // Plan cache helpers (api.cpp); the caller holds ctx->mu.
@@ -141,12 +122,6 @@ void free_plan(sparkcl_ctx *ctx, Plan *p);
 bool evict_one(sparkcl_ctx *ctx);
 // Arena block for plan p, evicting older plans while the arena is full.
 int arena_alloc(sparkcl_ctx *ctx, Plan *p, uint64_t bytes, void **out);
-// The cut of a call: a function of the call, the tuning table and the
-// executor occupancy; allocates nothing.
-Cut plan_cut(const sparkcl_ctx *ctx, int mode, const sparkcl_task *tasks, uint32_t ntasks,
-             bool host_in, uint32_t per_cu = 0);
-// The tile size of one task under a cut.
-uint32_t cut_tile(const sparkcl_ctx *ctx, const Cut &c, const sparkcl_task &t);
 // The device descriptor of one task.
 void fill_taskdev(const sparkcl_task &t, uint32_t variant, uint32_t tile, uint32_t ntiles,
                   uint32_t index, Partial *partials, uint32_t unroll, TaskDev *d);
@@ -180,42 +155,19 @@ void drop_plans(sparkcl_ctx *ctx);
 // Allocation-free workspace (noalloc.hip): looks up this device's address of
 // the fixed device array once per device; `device` must be current.
 int noalloc_setup(int device);
-// Persistent-executor grid for a batch holding the kernels in kid_mask
-// (bit k-1 for kernel id k) and `ntiles` tiles over `ntasks` tasks.
-uint32_t exec_grid(const sparkcl_ctx *ctx, uint32_t kid_mask, uint64_t ntiles = 0,
-                   uint64_t ntasks = 0, uint32_t block = 0);
-// The executor's threads per block for a batch holding the kernels in
-// kid_mask (one kernel: its tuned size; several: the mixed-batch size), and
-// the float4 loads in flight per thread for a kernel's streaming loop.
-uint32_t exec_block(const sparkcl_ctx *ctx, uint32_t kid_mask);
-// Executor blocks per CU that fit for a batch holding the kernels in
-// kid_mask (the Monte-Carlo-only instance fits more).
-uint32_t exec_occupancy(const sparkcl_ctx *ctx, uint32_t kid_mask);
-// Whether a batch holding the kernels in kid_mask runs the Monte-Carlo-only
-// executor instance (Monte-Carlo tasks alone).
-bool mc_instance(const sparkcl_ctx *ctx, uint32_t kid_mask);
-uint32_t kernel_unroll(const sparkcl_tuning &t, uint32_t kid);
 
 } // namespace sparkcl
 
-struct sparkcl_ctx {
+struct sparkcl_ctx : sparkcl::ExecEnv {
     int device = 0;
     std::string arch;
-    int cus = 0;
     uint32_t ns_per_tick = 10;
-    int occ_batch = 1; // batch-executor blocks per CU that fit
-    int occ_mc = 1;    // blocks per CU of the Monte-Carlo-only executor
-    // autotuner only: Monte-Carlo batches run the shared executor, so that
-    // blocks_per_cu[MC_PI] is measured where mixed batches use it
-    bool tune_shared_mc = false;
     int occ_chain = 1; // chain-executor blocks per CU that fit
 
     char *arena_base = nullptr;
     bool own_arena = false;
     sparkcl::Arena arena;
 
-    sparkcl_tuning tuning{};
-    bool own_tuning = false; // set by the caller: its tile tables are taken as they are
     sparkcl_config config{};
 
     std::mutex mu; // plans, events, pinned buffers
