@@ -1,8 +1,8 @@
 // C shim over the pure host logic (arena allocator, map-call overlap check,
-// the cut of a call into tiles, serving admission control, tuning table and
-// its JSON cache) so it can be unit-tested on a machine without a GPU.  Built
-// with g++ into libsparkcl_host.so; it is not part of the product library's
-// ABI.
+// the cut of a call into tiles and of its blocks into launches, serving
+// admission control, tuning table and its JSON cache) so it can be unit-tested
+// on a machine without a GPU.  Built with g++ into libsparkcl_host.so; it is
+// not part of the product library's ABI.
 #include <cstring>
 #include <map>
 #include <string>
@@ -10,6 +10,7 @@
 #include "admission.h"
 #include "arena.h"
 #include "cut.h"
+#include "launches.h"
 #include "overlap.h"
 #include "tuning.h"
 
@@ -64,6 +65,23 @@ int hl_cut(const sparkcl_tuning *t, uint32_t cus, uint32_t occ, int mode,
                       ? cut_tile(&env, c, tasks[i])
                       : 0;
     return c.even_bytes != 0;
+}
+
+// The launches that `blocks` blocks of `threads` threads take: their number, and
+// the first `cap` of them in first[] and count[].
+uint64_t hl_launches(uint64_t blocks, uint32_t threads, uint64_t *first, uint32_t *count,
+                     uint64_t cap)
+{
+    uint64_t n = 0;
+    (void)in_launches(blocks, threads, [&](uint64_t at, uint32_t c) {
+        if (n < cap) {
+            first[n] = at;
+            count[n] = c;
+        }
+        ++n;
+        return 0;
+    });
+    return n;
 }
 
 void *hl_adm_new(uint64_t budget, uint32_t slots, uint64_t tile_cap)

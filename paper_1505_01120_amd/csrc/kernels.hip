@@ -30,6 +30,7 @@
 
 #include <cstddef>
 
+#include "launches.h"
 #include "philox_dev.h"
 #include "sparkcl_dev.h"
 
@@ -2567,16 +2568,11 @@ int launch_map(const TaskDev *dtasks, uint32_t ntasks, uint64_t tile0, uint64_t 
 {
     if (ntasks == 0 || ntiles == 0)
         return SPARKCL_EINVAL;
-    constexpr uint64_t kMost = 1ull << 30; // blocks per launch
-    for (uint64_t at = 0; at < ntiles; at += kMost) {
-        const uint32_t grid = (uint32_t)(ntiles - at < kMost ? ntiles - at : kMost);
+    return in_launches(ntiles, kBlock, [&](uint64_t at, uint32_t grid) {
         hipLaunchKernelGGL(k_map, dim3(grid), dim3(kBlock), 0, (hipStream_t)stream, dtasks,
                            ntasks, tile0 + at);
-        const int rc = hip_status(hipGetLastError());
-        if (rc != SPARKCL_OK)
-            return rc;
-    }
-    return SPARKCL_OK;
+        return hip_status(hipGetLastError());
+    });
 }
 
 int launch_wc_pad(const uint8_t *text, uint64_t n, uint8_t *out, void *stream)
