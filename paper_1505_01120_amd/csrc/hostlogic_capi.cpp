@@ -1,8 +1,8 @@
 // C shim over the pure host logic (arena allocator, map-call overlap check,
-// the cut of a call into tiles and of its blocks into launches, serving
-// admission control, tuning table and its JSON cache) so it can be unit-tested
-// on a machine without a GPU.  Built with g++ into libsparkcl_host.so; it is
-// not part of the product library's ABI.
+// the cut of a call into tiles and of its blocks into launches, the passes of
+// an array reduce, serving admission control, tuning table and its JSON cache)
+// so it can be unit-tested on a machine without a GPU.  Built with g++ into
+// libsparkcl_host.so; it is not part of the product library's ABI.
 #include <cstring>
 #include <map>
 #include <string>
@@ -12,6 +12,7 @@
 #include "cut.h"
 #include "launches.h"
 #include "overlap.h"
+#include "treeplan.h"
 #include "tuning.h"
 
 using namespace sparkcl;
@@ -65,6 +66,20 @@ int hl_cut(const sparkcl_tuning *t, uint32_t cus, uint32_t occ, int mode,
                       ? cut_tile(&env, c, tasks[i])
                       : 0;
     return c.even_bytes != 0;
+}
+
+// The passes of an array reduce as {count, chunk, rows, cpt, threads, groups,
+// cols}: their number, the first `cap` of them in out.
+uint32_t hl_tree_passes(uint32_t k, uint64_t len, uint32_t cus, int least, uint32_t (*out)[7],
+                        uint32_t cap)
+{
+    const std::vector<TreePass> p = tree_passes(k, len, cus, least != 0);
+    for (uint32_t i = 0; i < p.size() && i < cap; ++i) {
+        const uint32_t v[7] = {p[i].count,   p[i].chunk,  p[i].rows, p[i].cpt,
+                               p[i].threads, p[i].groups, p[i].cols};
+        std::memcpy(out[i], v, sizeof(v));
+    }
+    return (uint32_t)p.size();
 }
 
 // The launches that `blocks` blocks of `threads` threads take: their number, and

@@ -202,6 +202,8 @@ constexpr uint32_t kTreeWideBig = 512;
 constexpr uint32_t kTreeFlatThreads = 1024;
 constexpr uint32_t kTreeFlatPer = 64;
 constexpr uint64_t kTreeCached = 256ull << 20;
+// Scratch that a pass of it may always take, whatever the column kernel needs.
+constexpr uint64_t kTreeScratch = 8ull << 20;
 int launch_tree(const TreeArgs &a, uint32_t combiner, void *stream);
 // WordCount: text of n bytes counted into the global open-addressing table
 // keys/counts of mask + 1 slots (a power of two, cleared beforehand); ctl[0]
