@@ -15,7 +15,7 @@ Produces, next to this file:
   probe_isa.json      -- VALU instructions per loop iteration of each VALU
                          probe, read from the probe library's own assembly;
   isa.json            -- resource figures of the kernels' own gfx950 code
-                         (registers, private segment, VALU instructions per
+                         (registers, LDS, private segment, VALU instructions per
                          Philox block), read from the device assembly of this
                          same build: the no-spill guard test and the
                          Monte-Carlo ALU roofline use them.
@@ -78,11 +78,11 @@ def isa_report(asm: str) -> dict:
     the Philox loop (the basic block of k_batch holding the most three-way
     xors) from the device assembly text."""
     out = {}
-    meta = asm[asm.find("amdhsa.kernels:"):]
+    entries = asm[asm.find("amdhsa.kernels:"):].split("\n  - ")
     for k in KERNELS:
         # a template kernel has one entry per instantiation: keep the worst
-        blocks = re.findall(r"\.name:\s+_ZN7sparkcl12_GLOBAL__N_1\d+" + k + r"[EI].*?(?=\n  - \.|\Z)",
-                            meta, re.S)
+        blocks = [e for e in entries
+                  if re.search(r"\.name:\s+_ZN7sparkcl12_GLOBAL__N_1\d+" + k + "[EI]", e)]
         if not blocks:
             continue
 
@@ -91,6 +91,7 @@ def isa_report(asm: str) -> dict:
             vals = [int(f.group(1)) for f in vals if f]
             return max(vals) if vals else None
         out[k] = {"vgpr": field("vgpr_count"), "sgpr": field("sgpr_count"),
+                  "lds_bytes": field("group_segment_fixed_size"),
                   "private_segment_bytes": field("private_segment_fixed_size"),
                   "vgpr_spills": field("vgpr_spill_count"),
                   "sgpr_spills": field("sgpr_spill_count")}

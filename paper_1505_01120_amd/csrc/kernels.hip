@@ -1271,6 +1271,56 @@ __device__ __forceinline__ T tree_fold(uint32_t m, Leaf leaf)
     return acc;
 }
 
+// The same over [0, m), m < 2^N, in fewer registers: the eights enter a counter
+// of N - 3 slots, the last m % 8 leaves are combined as subtrees of 4, 2 and 1,
+// and LOADS leaves (4 or 8) are in flight.
+template <uint32_t COMB, int N, int LOADS, class T, class Leaf>
+__device__ __forceinline__ T tree_fold_short(uint32_t m, Leaf leaf)
+{
+    T slot[N - 3];
+    auto half = [&](uint32_t i) -> T { // the subtree of 4 leaves
+        T v[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+            v[b] = leaf(i + b);
+        return comb<COMB>(comb<COMB>(v[0], v[1]), comb<COMB>(v[2], v[3]));
+    };
+    uint32_t i = 0;
+    for (; i + 8 <= m; i += 8) {
+        const T l = half(i);
+        if constexpr (LOADS == 4)
+            __asm__ volatile("" ::: "memory"); // the second half's loads after the first's
+        tree_insert<0, COMB>(slot, i >> 3, comb<COMB>(l, half(i + 4)));
+    }
+    T four{}, two{}, acc{};
+    bool have = false;
+    if (m & 4u) {
+        four = half(i);
+        i += 4;
+    }
+    if (m & 2u) {
+        const T a = leaf(i), b = leaf(i + 1);
+        two = comb<COMB>(a, b);
+        i += 2;
+    }
+    // smallest (rightmost) first
+    auto merge = [&](const T &left) {
+        acc = have ? comb<COMB>(left, acc) : left;
+        have = true;
+    };
+    if (m & 1u)
+        merge(leaf(i));
+    if (m & 2u)
+        merge(two);
+    if (m & 4u)
+        merge(four);
+#pragma unroll
+    for (int j = 0; j < N - 3; ++j)
+        if (m & (8u << j))
+            merge(slot[j]);
+    return acc;
+}
+
 template <uint32_t COMB>
 __global__ __launch_bounds__(kBlock) void k_tree(TreeArgs a)
 {
@@ -1297,18 +1347,23 @@ __global__ __launch_bounds__(kBlock) void k_tree(TreeArgs a)
 // With one thread per column alone, arrays shorter than a block's threads
 // leave most lanes idle and give each live one a long serial chain.  Bound by
 // HBM or the memory-side cache for large inputs, by the launches and the last
-// pass (one block) below some 20 MB.  Measured on MI355X, before and now:
-// 2^20 rows of 24 floats 279 -> 28 us, of 64 176 -> 49 us, of 255 237 -> 233
-// us; 4000 rows of 1024 floats 29 -> 10 us.  The rows of a group are
-// neighbours, so the loads of its 8 steps share cache lines and repeated
-// inputs stay in the memory-side cache: plain loads, except NT, for inputs
-// that exceed that cache (2^20 rows of 64 floats, 256 MiB: 57 us plain, 68
-// nontemporal; 131072 rows of 2047, 1 GiB: 217 and 206).
+// pass (one block) below some 20 MB.  At 64 registers two blocks of 1024
+// threads fit a CU, or one beside two blocks of the resident serving executor;
+// so the eights' counter is kept short (tree_fold_short), and a pointer table,
+// whose pointers take registers of their own, has 4 loads in flight (8 for
+// rows).  Measured on MI355X, in columns, with 80 registers and with 64: 2^20
+// rows of 255 floats 260, 254 and 216 us; 5.6 10^6 rows of 24 722, 172 and
+// 120; 268435 rows of 1000 211, 225 and 195; 2048 rows of 4096 18.3, 9.9 and
+// 9.4.  The rows of a group are neighbours, so the loads of its 8 steps share
+// cache lines and repeated inputs stay in the memory-side cache: plain loads,
+// except NT, for inputs that exceed that cache (2^20 rows of 64 floats, 256
+// MiB: 57 us plain, 68 nontemporal; 131072 rows of 2047, 1 GiB: 217 and 206;
+// both with 80 registers).
 constexpr int kTreeFlatSlots = 7; // up to 2^6 leaves per group
 static_assert(kTreeFlatPer == 1u << (kTreeFlatSlots - 1), "a group's leaves fit the counter");
 
-template <int V, uint32_t COMB, bool NT>
-__global__ __launch_bounds__(kTreeFlatThreads) void k_tree_flat(TreeArgs a)
+template <int V, uint32_t COMB, bool NT, bool PTRS>
+__global__ __launch_bounds__(kTreeFlatThreads, 8) void k_tree_flat(TreeArgs a)
 {
     typedef TreeVec<V> TV;
     typedef typename TV::T T;
@@ -1325,9 +1380,9 @@ __global__ __launch_bounds__(kTreeFlatThreads) void k_tree_flat(TreeArgs a)
     const uint32_t mb = min(a.count - k0, a.chunk);
     const uint32_t g0 = g * per;
     const uint32_t m = live && g0 < mb ? min(per, mb - g0) : 0;
-    T acc = tree_fold<COMB, kTreeFlatSlots, T>(m, [&](uint32_t i) -> T {
+    T acc = tree_fold_short<COMB, kTreeFlatSlots, PTRS ? 4 : 8, T>(m, [&](uint32_t i) -> T {
         const uint32_t kk = k0 + g0 + i;
-        const float *p = (a.ptrs ? a.ptrs[kk] : a.base + (uint64_t)kk * a.stride) + col;
+        const float *p = (PTRS ? a.ptrs[kk] : a.base + (uint64_t)kk * a.stride) + col;
         if constexpr (NT) {
             return TV::ld(p);
         } else if constexpr (V == 4) {
@@ -2656,12 +2711,19 @@ int launch_tree(const TreeArgs &a, uint32_t combiner, void *stream)
             return SPARKCL_EINVAL;
         const dim3 grid(nchunks, (uint32_t)tiles), block(a.threads);
         const bool nt = a.len >= 4 && a.len * a.count * 4 > kTreeCached;
+#define SPARKCL_FLAT_AS(V, COMB, NT)                                           \
+    do {                                                                       \
+        if (a.ptrs)                                                            \
+            hipLaunchKernelGGL((k_tree_flat<V, COMB, NT, true>), grid, block, 0, s, a); \
+        else                                                                   \
+            hipLaunchKernelGGL((k_tree_flat<V, COMB, NT, false>), grid, block, 0, s, a); \
+    } while (0)
 #define SPARKCL_FLAT(V, NT)                                                    \
     do {                                                                       \
         if (add)                                                               \
-            hipLaunchKernelGGL((k_tree_flat<V, SPARKCL_VADD, NT>), grid, block, 0, s, a); \
+            SPARKCL_FLAT_AS(V, SPARKCL_VADD, NT);                              \
         else                                                                   \
-            hipLaunchKernelGGL((k_tree_flat<V, SPARKCL_VMAX, NT>), grid, block, 0, s, a); \
+            SPARKCL_FLAT_AS(V, SPARKCL_VMAX, NT);                              \
     } while (0)
         if (a.len < 4)
             SPARKCL_FLAT(1, false);
@@ -2670,6 +2732,7 @@ int launch_tree(const TreeArgs &a, uint32_t combiner, void *stream)
         else
             SPARKCL_FLAT(4, false);
 #undef SPARKCL_FLAT
+#undef SPARKCL_FLAT_AS
         return hip_status(hipGetLastError());
     }
     if (a.len < 4 || a.chunk > (1u << (kTreeSlots - 1)) || nchunks > 65535)
