@@ -1534,8 +1534,12 @@ __global__ __launch_bounds__(kBlock) void k_zero(uint32_t *p, uint64_t words)
 // overflow a spill region, go to the table with atomics.  Counts are integers,
 // so the result does not depend on which block counts which word.
 //
-// One block of 16 waves per CU shares one table of 8192 keys: four blocks of
-// 2048 keys each would hold the same few frequent words four times over.
+// Two blocks of 8 waves per CU with tables of 4096 keys: smaller ones hold the
+// same few frequent words several times over (four of 2048 keys), and one of 16
+// waves and 8192 keys, 1 to 5% faster on 16 MiB and more (512 MiB, 10^5 words:
+// 544 us against 558 a call; first occurrences in 256 MiB 463 and 489), can't
+// start on a CU that holds a block of the resident serving executor, whose
+// registers leave room for one of 8 waves.
 //
 // Measured on MI355X, 512 MiB of Zipf text (10^5 words), whole call with its
 // sort of the keys: 1400-1575 us with one word per lane hashed byte by byte
@@ -1543,14 +1547,16 @@ __global__ __launch_bounds__(kBlock) void k_zero(uint32_t *p, uint64_t words)
 // MiB of 2 10^5 words 4350 and 455 us.  Of the scan's 435 us its walk takes 320
 // without a word kept; places 55; the second queue and the tables written
 // out whole took 150 off what misses and atomics cost.
-constexpr int kWcBlock = (int)kWcWaves * 64;
+constexpr int kWcScanBlock = (int)kWcWaves * 64;
+constexpr int kWcBlock = 1024; // of the merge and the compaction
+constexpr uint32_t kWcBlockWaves = kWcBlock / 64;
 constexpr uint32_t kWcQueue = 64 + 4 * 64; // a wave's waiting words: 8 steps end
                                            // at most 4 per lane
 constexpr uint32_t kWcCompact = 4 * kWcBlock; // table slots of a compaction block
 constexpr uint32_t kWcMissed = 2 * 64;     // those that found no place in the table
 constexpr uint32_t kWcPartSets = kWcSets >> kWcPartBits;
 // Locating keeps offsets beside the words, so its table is smaller.
-constexpr uint32_t kWlSets = 3072;
+constexpr uint32_t kWlSets = 1536;
 
 __device__ __forceinline__ bool wc_space(uint32_t b)
 {
@@ -1595,8 +1601,8 @@ __device__ void wc_global_add(const WcArgs &a, uint64_t h, uint64_t c)
 }
 
 // The LDS counts are 32-bit: a block counts at most one word per two bytes
-// of the text it scans, and a block scans either a few KiB or about 1/256 of
-// the text (a grid of one block per CU), which is limited to 2^40 bytes.
+// of the text it scans, and a block scans either a few KiB or about 1/512 of
+// the text (a grid of two blocks per CU), which is limited to 2^40 bytes.
 // A word that found no LDS slot: appended to this block's spill region of
 // its partition, or, when the region is full (or there are none, or its key
 // is 0), added to the table directly.  scnt: the block's per-partition
@@ -2025,17 +2031,17 @@ __device__ __forceinline__ uint64_t wc_scan(const uint8_t *text, uint64_t n, uin
     return words;
 }
 
-__global__ __launch_bounds__(kWcBlock) void k_wordcount(WcArgs a)
+__global__ __launch_bounds__(kWcScanBlock, 4) void k_wordcount(WcArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint64_t sk[kWcSlots];
     __shared__ uint32_t sc[kWcSlots];
     __shared__ uint32_t scnt[1u << kWcPartBits];    // spill appends per partition
     const uint32_t tid = threadIdx.x;
-    for (uint32_t i = tid; i < kWcSlots; i += kWcBlock) {
+    for (uint32_t i = tid; i < kWcSlots; i += kWcScanBlock) {
         sk[i] = 0;
         sc[i] = 0;
     }
-    for (uint32_t i = tid; i < (1u << kWcPartBits); i += kWcBlock)
+    for (uint32_t i = tid; i < (1u << kWcPartBits); i += kWcScanBlock)
         scnt[i] = 0;
     __syncthreads();
     const uint64_t words = wc_scan<false>(
@@ -2055,14 +2061,14 @@ __global__ __launch_bounds__(kWcBlock) void k_wordcount(WcArgs a)
         // the table as it stands, for the merge: a set's slots hold the same
         // partition's keys in every block
         const uint64_t row = (uint64_t)blockIdx.x * kWcSlots;
-        for (uint32_t i = tid; i < kWcSlots; i += kWcBlock) {
+        for (uint32_t i = tid; i < kWcSlots; i += kWcScanBlock) {
             a.table_keys[row + i] = sk[i];
             a.table_counts[row + i] = sc[i];
         }
-        for (uint32_t p = tid; p < (1u << kWcPartBits); p += kWcBlock)
+        for (uint32_t p = tid; p < (1u << kWcPartBits); p += kWcScanBlock)
             a.spill_cnt[((uint64_t)blockIdx.x << kWcPartBits) | p] = min(scnt[p], a.spill_cap);
     } else {
-        for (uint32_t i = tid; i < kWcSlots; i += kWcBlock)
+        for (uint32_t i = tid; i < kWcSlots; i += kWcScanBlock)
             if (sk[i])
                 wc_global_add(a, sk[i], sc[i]);
     }
@@ -2158,11 +2164,11 @@ __device__ __forceinline__ void wl_lookup(const WlArgs &l, uint64_t h, uint64_t 
     }
 }
 
-__global__ __launch_bounds__(kWcBlock) void k_wl_scan(WlArgs l)
+__global__ __launch_bounds__(kWcScanBlock, 4) void k_wl_scan(WlArgs l)
 {
     __shared__ __attribute__((aligned(16))) uint64_t sk[2 * kWlSets];
     __shared__ uint32_t sv[2 * kWlSets]; // lowest offset / 256 taken to the table (n <= 2^40)
-    for (uint32_t i = threadIdx.x; i < 2 * kWlSets; i += kWcBlock) {
+    for (uint32_t i = threadIdx.x; i < 2 * kWlSets; i += kWcScanBlock) {
         sk[i] = 0;
         sv[i] = ~0u;
     }
@@ -2195,15 +2201,17 @@ __global__ __launch_bounds__(kWcBlock) void k_wl_scan(WlArgs l)
 // spent most of 200 us on them.
 //
 // A wave takes one scan block's region at a time, K keys per lane, with the
-// next region's keys in flight.
-constexpr uint32_t kWcMergeSlots = 8192;
+// next region's keys in flight.  72 KiB of LDS: a block of 96 KiB does not
+// start on a CU that holds two blocks of the serving executor, small as their
+// own LDS is.
+constexpr uint32_t kWcMergeSlots = 6144;
 constexpr uint32_t kWcMergeProbes = 8;
 
 // The slot of key h (not 0) in the merge's table, or kNoSlot.
 __device__ __forceinline__ uint32_t wc_merge_place(uint64_t *mk, uint64_t h)
 {
     // (other bits of the key make the partition)
-    uint32_t s = (uint32_t)(h >> 32) & (kWcMergeSlots - 1);
+    uint32_t s = __umulhi((uint32_t)(h >> 32), kWcMergeSlots);
     for (uint32_t q = 0; q < kWcMergeProbes; ++q) {
         uint64_t key = mk[s];
         if (key == 0) {
@@ -2212,7 +2220,7 @@ __device__ __forceinline__ uint32_t wc_merge_place(uint64_t *mk, uint64_t h)
         }
         if (key == h)
             return s;
-        s = (s + 1) & (kWcMergeSlots - 1);
+        s = s + 1 == kWcMergeSlots ? 0 : s + 1;
     }
     return kNoSlot;
 }
@@ -2234,13 +2242,13 @@ __device__ __forceinline__ void wc_merge_regions(const WcArgs &a, uint32_t scan_
         from = at + 64 * K;
     };
     // 64 regions' counts at a time
-    for (uint32_t b0 = wave; b0 < scan_grid; b0 += 64 * kWcWaves) {
-        const uint32_t mine = b0 + lane * kWcWaves;
+    for (uint32_t b0 = wave; b0 < scan_grid; b0 += 64 * kWcBlockWaves) {
+        const uint32_t mine = b0 + lane * kWcBlockWaves;
         const uint32_t counts =
             mine < scan_grid ? a.spill_cnt[((uint64_t)mine << kWcPartBits) | p] : 0;
-        const uint32_t regions = min(64u, (scan_grid - b0 + kWcWaves - 1) / kWcWaves);
+        const uint32_t regions = min(64u, (scan_grid - b0 + kWcBlockWaves - 1) / kWcBlockWaves);
         auto region = [&](uint32_t at) -> uint64_t {
-            return (((uint64_t)(b0 + at * kWcWaves) << kWcPartBits) | p) * a.spill_cap;
+            return (((uint64_t)(b0 + at * kWcBlockWaves) << kWcPartBits) | p) * a.spill_cap;
         };
         uint32_t j = 0;
         load(region(0), __builtin_amdgcn_readlane(counts, 0));
@@ -2312,7 +2320,7 @@ __global__ __launch_bounds__(kWcBlock) void k_wc_merge(WcArgs a, uint32_t scan_g
 __global__ __launch_bounds__(kWcBlock) void k_wc_compact(WcArgs a, uint64_t *out_keys,
                                                          uint64_t *out_counts, uint64_t cap)
 {
-    __shared__ uint32_t sh_wave[kWcWaves];
+    __shared__ uint32_t sh_wave[kWcBlockWaves];
     __shared__ uint64_t sh_base;
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const uint64_t first = (uint64_t)blockIdx.x * kWcCompact + threadIdx.x;
@@ -2331,7 +2339,7 @@ __global__ __launch_bounds__(kWcBlock) void k_wc_compact(WcArgs a, uint64_t *out
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t total = 0;
-        for (uint32_t w = 0; w < kWcWaves; ++w) {
+        for (uint32_t w = 0; w < kWcBlockWaves; ++w) {
             const uint32_t n = sh_wave[w];
             sh_wave[w] = total;
             total += n;
@@ -2646,7 +2654,7 @@ int launch_wordcount(const WcArgs &a, uint32_t grid, void *stream)
         a.span == 0 || a.span % 16 != 0 ||
         a.span > kWcMaxSpan)
         return SPARKCL_EINVAL;
-    hipLaunchKernelGGL(k_wordcount, dim3(grid), dim3(kWcBlock), 0, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(k_wordcount, dim3(grid), dim3(kWcScanBlock), 0, (hipStream_t)stream, a);
     return hip_status(hipGetLastError());
 }
 
@@ -2681,7 +2689,7 @@ int launch_wordcount_locate(const WlArgs &l, uint32_t scan_grid, void *stream)
     hipLaunchKernelGGL(k_wl_build, keys, dim3(kBlock), 0, s, l);
     int rc = hip_status(hipGetLastError());
     if (rc == SPARKCL_OK && l.n != 0) {
-        hipLaunchKernelGGL(k_wl_scan, dim3(scan_grid), dim3(kWcBlock), 0, s, l);
+        hipLaunchKernelGGL(k_wl_scan, dim3(scan_grid), dim3(kWcScanBlock), 0, s, l);
         rc = hip_status(hipGetLastError());
     }
     if (rc == SPARKCL_OK) {

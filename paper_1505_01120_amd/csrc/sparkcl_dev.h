@@ -217,12 +217,13 @@ int launch_tree(const TreeArgs &a, uint32_t combiner, void *stream);
 // merge kernel then counts each partition's keys in LDS and adds each distinct
 // key to the global table once.  spill_cap 0: no spill regions (every miss,
 // and every key of the block's table, goes to the global table directly).
-constexpr uint32_t kWcSets = 4096;
+constexpr uint32_t kWcSets = 2048;
 constexpr uint32_t kWcSlots = 2 * kWcSets;
 constexpr uint32_t kWcPartBits = 8;
-// Scan blocks are kWcWaves waves, one block per CU; a lane's span of text is at
-// most kWcMaxSpan bytes, for locating kWlMaxSpan.
-constexpr uint32_t kWcWaves = 16;
+// Scan blocks are kWcWaves waves, kWcPerCu blocks per CU; a lane's span of text
+// is at most kWcMaxSpan bytes, for locating kWlMaxSpan.
+constexpr uint32_t kWcWaves = 8;
+constexpr uint32_t kWcPerCu = 2;
 constexpr uint32_t kWcMaxSpan = 4096;
 constexpr uint32_t kWlMaxSpan = 256;
 static_assert(64 * kWlMaxSpan <= 1u << 16, "queued offsets are 16 bits");

@@ -14,19 +14,20 @@ using namespace sparkcl;
 namespace {
 
 // The scan's geometry: bytes of text per lane and chunk, and blocks.  Equal
-// shares for all lanes of one block per CU, cut into as few chunks as `most`
+// shares for all lanes of kWcPerCu blocks per CU, cut into as few chunks as `most`
 // allows (16 steps past each span's end are spent on words that
 // cross it); a text too short for 16 bytes per lane takes fewer blocks, whose
 // waves share their tables.
 void scan_geometry(const sparkcl_ctx *ctx, uint64_t nbytes, uint32_t most, uint32_t *span,
                    uint32_t *grid)
 {
-    const uint64_t lanes = 64ull * kWcWaves * (uint64_t)ctx->cus;
+    const uint64_t blocks = (uint64_t)kWcPerCu * (uint64_t)ctx->cus;
+    const uint64_t lanes = 64ull * kWcWaves * blocks;
     const uint64_t per = std::max<uint64_t>(1, (nbytes + lanes - 1) / lanes);
     const uint64_t sweeps = (per + most - 1) / most;
     *span = (uint32_t)(((per + sweeps - 1) / sweeps + 15) / 16 * 16);
     const uint64_t chunks = std::max<uint64_t>(1, (nbytes + 64ull * *span - 1) / (64ull * *span));
-    *grid = (uint32_t)std::min<uint64_t>((chunks + kWcWaves - 1) / kWcWaves, (uint64_t)ctx->cus);
+    *grid = (uint32_t)std::min<uint64_t>((chunks + kWcWaves - 1) / kWcWaves, blocks);
 }
 
 } // namespace
@@ -159,7 +160,7 @@ int sparkcl_wordcount_locate(sparkcl_ctx *ctx, const uint8_t *text, uint64_t nby
     // little by them: shorter ones while there would be fewer than four chunks
     // (100 MiB: 246 us in two of 192 bytes, 226 in three of 128; 256 MiB: 463 in
     // four of 256, 467 in eight of 128).
-    const uint64_t lanes = 64ull * kWcWaves * (uint64_t)ctx->cus;
+    const uint64_t lanes = 64ull * kWcWaves * kWcPerCu * (uint64_t)ctx->cus;
     scan_geometry(ctx, nbytes, nbytes < 4 * kWlMaxSpan * lanes ? kWlMaxSpan / 2 : kWlMaxSpan,
                   &span, &grid);
     // the table, then the control words; a small one (some 2 MiB at most, half

@@ -64,3 +64,16 @@ def check(ctx, named):
 
 def test_calls_beside_serving(ctx):
     check(ctx, calls(ctx))
+
+
+@pytest.mark.parametrize("nbytes", [1 << 12, 1 << 20, 1 << 26])
+def test_wordcount_beside_serving(ctx, nbytes):
+    g = torch.Generator(device="cuda").manual_seed(nbytes)
+    text = torch.randint(97, 123, (nbytes,), device="cuda", generator=g).to(torch.uint8)
+    text[::4] = 32
+    cap = 1 << 15
+    keys, counts, distinct, _ = ctx.wordcount(text, cap)
+    found = keys[:distinct].clone()
+    offsets = torch.empty_like(found)
+    check(ctx, [("word count", lambda: ctx.wordcount(text, cap, keys, counts)),
+                ("locate", lambda: ctx.wordcount_locate(text, found, offsets=offsets))])
