@@ -255,7 +255,7 @@ int launch_wc_compact(const WcArgs &a, uint64_t *keys, uint64_t *counts, uint64_
 // first word with that key (UINT64_MAX if none), through a lookup table of
 // at least 3/2 nkeys slots (cleared to 0, and ctl[0..1], beforehand).  ctl[0]:
 // index + 1 of the key 0; ctl[1]: set when a key repeats; ctl[2]: the offset of
-// the key 0.
+// the key 0; ctl[3]: scan blocks that have ended.
 struct WlSlot {
     uint64_t key; // 0: empty
     uint64_t off;
