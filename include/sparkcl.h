@@ -389,7 +389,11 @@ typedef struct sparkcl_tuning {
     /* tile size in elements (samples for MC_PI) for [mode][kernel-1][log2 n];
        powers of two from 2^10 to 2^22.  A batched call whose executor blocks
        would get fewer than two of the batched row's tiles each is cut with
-       the per-launch row instead. */
+       the per-launch row instead; or, if it holds no Monte-Carlo task and the
+       per-launch rows of POLY and FMUL are the built-in ones or those that
+       sparkcl_autotune or a cache file it wrote ("small_by_time": 1) put in
+       force, into tiles of least estimated time, since those rows are tuned
+       on single tasks. */
     uint32_t tile[SPARKCL_TUNE_MODES][3][SPARKCL_TUNE_BUCKETS];
 } sparkcl_tuning;
 
@@ -434,7 +438,8 @@ typedef struct sparkcl_launch_shape {
                              own tuned size)                                */
     uint32_t ntiles;      /* tiles the call was cut into                    */
     uint32_t ntasks;
-    uint32_t tile_table;  /* 0: the per-launch tile table, 1: the batched one */
+    uint32_t tile_table;  /* 0: the per-launch tile table, or tiles cut by
+                             estimated time; 1: the batched one             */
     uint32_t mixed;       /* 1: cut with the mixed-batch tiles (tile_many or
                              many_tiles_per_cu)                            */
     uint32_t mode;        /* SPARKCL_PER_LAUNCH, _BATCHED or _GRAPH         */
@@ -490,8 +495,8 @@ SPARKCL_API int sparkcl_offload_breakeven(sparkcl_ctx *ctx, double host_bytes_pe
 /* For callers that cannot allocate device memory when they call (tight
    serving loops, harnesses that forbid allocation): the batched ReduceCL of
    sparkcl_reduce_async(..., SPARKCL_BATCHED, ...) -- cut into the same tiles
-   under ctx's tuning table and occupancy, so its results are bit-identical
-   to that call's -- with every workspace it needs (task table, tile queue,
+   under ctx's tuning table (and whether its rows are the caller's) and
+   occupancy, so its results are bit-identical to that call's -- with every workspace it needs (task table, tile queue,
    partials, arrival tickets, queue counters, internal results) in one fixed
    array of SPARKCL_NOALLOC_SCRATCH_BYTES of device memory that the library
    holds on each GPU it runs on until the process ends, instead of blocks of

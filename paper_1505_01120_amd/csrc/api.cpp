@@ -833,11 +833,14 @@ int sparkcl_init(const sparkcl_config *config, sparkcl_ctx **out)
     ctx->occ_chain = std::max(1, occ);
 
     tuning_defaults(&ctx->tuning);
+    ctx->rows_are_tuned(true);
     if (config->tune_cache) {
         std::string err;
-        sparkcl_tuning t;
-        if (tuning_load_file(config->tune_cache, ctx->arch, &t, &err))
+        TunedTable t;
+        if (tuning_load_file(config->tune_cache, ctx->arch, &t, &err)) {
             ctx->tuning = t;
+            ctx->rows_are_tuned(t.small_by_time);
+        }
         // a missing or foreign cache keeps the defaults
     }
 
@@ -1118,7 +1121,6 @@ int sparkcl_set_tuning(sparkcl_ctx *ctx, const sparkcl_tuning *in)
     std::lock_guard<std::mutex> g(ctx->mu);
     drop_plans(ctx);
     ctx->tuning = *in;
-    ctx->own_tuning = true;
     if (ctx->server)
         ctx->server->set_tuning(*in);
     return SPARKCL_OK;

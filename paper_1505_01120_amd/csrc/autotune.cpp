@@ -178,7 +178,7 @@ extern "C" int sparkcl_autotune(sparkcl_ctx *ctx, uint32_t lo_log2, uint32_t hi_
     }
 
     sparkcl_tuning best = ctx->tuning;
-    ctx->own_tuning = true; // candidates are measured as the tables say
+    const sparkcl_tuning before = ctx->tuning;
     const bool verbose = std::getenv("SPARKCL_AUTOTUNE_LOG") != nullptr;
     // Times `tasks` under tuning `t`; false (with rc set) on failure.
     auto measure = [&](const sparkcl_tuning &t, int mode,
@@ -205,7 +205,7 @@ extern "C" int sparkcl_autotune(sparkcl_ctx *ctx, uint32_t lo_log2, uint32_t hi_
     };
     auto abort_with = [&](int code) {
         ctx->tune_shared_mc = false;
-        ctx->tuning = best;
+        ctx->tuning = before;
         cleanup();
         return code;
     };
@@ -444,12 +444,16 @@ extern "C" int sparkcl_autotune(sparkcl_ctx *ctx, uint32_t lo_log2, uint32_t hi_
     }
 
     ctx->tuning = best;
+    ctx->rows_are_tuned(true);
     if (ctx->server)
         ctx->server->set_tuning(best);
     cleanup();
     if (path) {
         std::string err;
-        if (!tuning_save_file(path, ctx->arch, best, &err))
+        TunedTable t;
+        static_cast<sparkcl_tuning &>(t) = best;
+        t.small_by_time = true;
+        if (!tuning_save_file(path, ctx->arch, t, &err))
             return fail(SPARKCL_EINVAL, err);
     }
     return SPARKCL_OK;

@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 
 #include "sparkcl_dev.h"
 
@@ -11,6 +12,20 @@ namespace sparkcl {
 uint64_t input_bytes(uint32_t kernel_id)
 {
     return kernel_id == SPARKCL_FMUL ? 8ull : 4ull;
+}
+
+void ExecEnv::rows_are_tuned(bool tuned)
+{
+    static_assert(SPARKCL_POLY == 1 && SPARKCL_FMUL == 2, "the first two kernels' rows");
+    if (tuned)
+        std::memcpy(tuned_rows, tuning.tile[TM_PER_LAUNCH], sizeof(tuned_rows));
+    else
+        std::memset(tuned_rows, 0, sizeof(tuned_rows));
+}
+
+bool ExecEnv::small_by_time() const
+{
+    return std::memcmp(tuned_rows, tuning.tile[TM_PER_LAUNCH], sizeof(tuned_rows)) == 0;
 }
 
 uint32_t exec_block(const ExecEnv *ctx, uint32_t kid_mask)
@@ -106,7 +121,7 @@ uint32_t even_tile(const sparkcl_task &t, uint64_t bytes)
 // elements 125 and 90 us, as a chain of three maps 179 and 126; 48 POLY tasks
 // of 300007 41 and 33 (with their values written 44 and 41); 256 of 20001 29
 // and 22; 16 of 10^6 with values 56 and 39.  Batches with Monte-Carlo tasks,
-// which compute, stay with the table, and so do tables that the caller set.
+// which compute, stay with the table, and so do rows that the caller set.
 void even_cut(const ExecEnv *ctx, const sparkcl_task *tasks, uint32_t ntasks, uint32_t mask,
               uint32_t per_cu, Cut *c)
 {
@@ -222,7 +237,7 @@ Cut plan_cut(const ExecEnv *ctx, int mode, const sparkcl_task *tasks,
             c.tm = TM_PER_LAUNCH;
             c.mixed = false;
             c.share_tile[0] = c.share_tile[1] = c.share_tile[2] = 0;
-            if (!ctx->own_tuning)
+            if (ctx->small_by_time())
                 even_cut(ctx, tasks, ntasks, mask, per_cu, &c);
         }
     }

@@ -39,13 +39,23 @@ struct ExecEnv {
     bool tune_shared_mc = false;
     uint32_t exec_blocks_per_cu = 0; // the caller's; 0: the tuned value
     sparkcl_tuning tuning{};
-    bool own_tuning = false; // set by the caller: its tile tables are taken as they are
+    // The per-launch rows of the streaming kernels that were tuned on single
+    // tasks: the built-in ones, or those that the autotuner or its cache file
+    // put in force (0: none).  While they are the table's, small batches are
+    // cut by estimated time; rows that the caller set are the cut.  So a table
+    // read and set again changes nothing, a tuned context and one that loads
+    // its cache file cut alike, and a row changed and changed back counts as
+    // unchanged.
+    uint32_t tuned_rows[2][SPARKCL_TUNE_BUCKETS] = {};
+
+    void rows_are_tuned(bool tuned);
+    bool small_by_time() const;
 };
 
 // Input bytes a streaming kernel reads per element (x, and y for FMUL).
 uint64_t input_bytes(uint32_t kernel_id);
-// The cut of a call: a function of the call, the tuning table and the
-// executor occupancy; allocates nothing.
+// The cut of a call: a function of the call and the ExecEnv; allocates
+// nothing.
 Cut plan_cut(const ExecEnv *ctx, int mode, const sparkcl_task *tasks, uint32_t ntasks,
              bool host_in, uint32_t per_cu = 0);
 // The tile size of one task under a cut.

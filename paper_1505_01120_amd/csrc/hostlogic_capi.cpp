@@ -51,14 +51,19 @@ int hl_tasks_independent(const sparkcl_task *tasks, uint32_t ntasks)
 }
 
 // The cut of a call on a device of `cus` CUs that fit `occ` executor blocks
-// each: 1 if it is cut by estimated time, else 0; each task's tile size in
-// tile[] (0 for an unknown kernel id).
-int hl_cut(const sparkcl_tuning *t, uint32_t cus, uint32_t occ, int mode,
-           const sparkcl_task *tasks, uint32_t ntasks, uint32_t per_cu, uint32_t *tile)
+// each, under table t with the rows of `tuned` (NULL: none) as tuned rows: 1 if
+// it is cut by estimated time, else 0; each task's tile size in tile[] (0 for
+// an unknown kernel id).
+int hl_cut(const sparkcl_tuning *t, const sparkcl_tuning *tuned, uint32_t cus, uint32_t occ,
+           int mode, const sparkcl_task *tasks, uint32_t ntasks, uint32_t per_cu, uint32_t *tile)
 {
     ExecEnv env;
     env.cus = (int)cus;
     env.occ_batch = env.occ_mc = (int)occ;
+    if (tuned) {
+        env.tuning = *tuned;
+        env.rows_are_tuned(true);
+    }
     env.tuning = *t;
     const Cut c = plan_cut(&env, mode, tasks, ntasks, false, per_cu);
     for (uint32_t i = 0; i < ntasks; ++i)
@@ -217,16 +222,35 @@ uint32_t hl_tile_for(const sparkcl_tuning *t, int mode, uint32_t kid, uint64_t n
 uint32_t hl_size_bucket(uint64_t n) { return size_bucket(n); }
 int hl_tuning_save(const char *path, const char *arch, const sparkcl_tuning *t)
 {
-    return tuning_save_file(path, arch, *t, nullptr) ? 1 : 0;
+    TunedTable table;
+    static_cast<sparkcl_tuning &>(table) = *t;
+    return tuning_save_file(path, arch, table, nullptr) ? 1 : 0;
 }
 int hl_tuning_load(const char *path, const char *arch, sparkcl_tuning *t)
 {
-    return tuning_load_file(path, arch, t, nullptr) ? 1 : 0;
+    TunedTable table;
+    if (!tuning_load_file(path, arch, &table, nullptr))
+        return 0;
+    *t = table;
+    return 1;
+}
+// Saves a table with its small_by_time and loads it back: the flag as read, or
+// -1.
+int hl_tuning_small_by_time(const char *path, const char *arch, const sparkcl_tuning *t, int flag)
+{
+    TunedTable table;
+    static_cast<sparkcl_tuning &>(table) = *t;
+    table.small_by_time = flag != 0;
+    TunedTable back;
+    if (!tuning_save_file(path, arch, table, nullptr) ||
+        !tuning_load_file(path, arch, &back, nullptr))
+        return -1;
+    return back.small_by_time ? 1 : 0;
 }
 // Parses `json`; returns the number of arch entries, or -1 with the reason in err.
 int hl_tuning_parse(const char *json, char *err, size_t errcap)
 {
-    std::map<std::string, sparkcl_tuning> all;
+    std::map<std::string, TunedTable> all;
     std::string e;
     if (!tuning_parse_json(json, &all, &e)) {
         if (err && errcap) {

@@ -4,8 +4,8 @@
 // arrival tickets, queue counters and internal results -- in one fixed array
 // of device memory instead of blocks of the context's arena, for callers that
 // cannot allocate.  The decomposition is the same function of the call, the
-// tuning table and the occupancy as in sparkcl_reduce_async, so the results
-// are bit-identical to it.
+// tuning table (and whether its rows are the caller's) and the occupancy as in
+// sparkcl_reduce_async, so the results are bit-identical to it.
 //
 // The array is a file-scope __device__ object: each GPU the library runs on
 // holds its own copy, at its own address, until the process ends.  Host code

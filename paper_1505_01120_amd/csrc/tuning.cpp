@@ -279,7 +279,7 @@ uint32_t tile_for(const sparkcl_tuning &t, int mode, uint32_t kid, uint64_t n)
 }
 
 bool tuning_parse_json(const std::string &text,
-                       std::map<std::string, sparkcl_tuning> *out, std::string *err)
+                       std::map<std::string, TunedTable> *out, std::string *err)
 {
     Parser p(text);
     Json root;
@@ -294,7 +294,7 @@ bool tuning_parse_json(const std::string &text,
         return false;
     }
     for (auto &arch : root.obj) {
-        sparkcl_tuning t;
+        TunedTable t;
         tuning_defaults(&t);
         const Json &e = arch.second;
         if (e.kind != Json::OBJ) {
@@ -331,6 +331,8 @@ bool tuning_parse_json(const std::string &text,
             for (int k = 0; k < 3; ++k)
                 (name[0] == 'b' ? t.block : t.unroll)[k] = (uint32_t)b->arr[k].num;
         }
+        if (const Json *b = e.get("small_by_time"))
+            t.small_by_time = b->num != 0;
         if (const Json *b = e.get("block_many"))
             t.block_many = (uint32_t)b->num;
         if (const Json *b = e.get("many_tiles_per_cu")) {
@@ -382,13 +384,13 @@ bool tuning_parse_json(const std::string &text,
     return true;
 }
 
-std::string tuning_to_json(const std::map<std::string, sparkcl_tuning> &all)
+std::string tuning_to_json(const std::map<std::string, TunedTable> &all)
 {
     std::ostringstream o;
     o << "{\n";
     size_t ai = 0;
     for (auto &kv : all) {
-        const sparkcl_tuning &t = kv.second;
+        const TunedTable &t = kv.second;
         o << " \"" << kv.first << "\": {\n  \"blocks_per_cu\": [" << t.blocks_per_cu[0]
           << ", " << t.blocks_per_cu[1] << ", " << t.blocks_per_cu[2]
           << "],\n  \"blocks_per_cu_many\": " << t.blocks_per_cu_many
@@ -398,7 +400,8 @@ std::string tuning_to_json(const std::map<std::string, sparkcl_tuning> &all)
           << t.block[2] << "],\n  \"block_many\": " << t.block_many << ",\n  \"unroll\": ["
           << t.unroll[0] << ", " << t.unroll[1] << ", " << t.unroll[2]
           << "],\n  \"many_tiles_per_cu\": [" << t.many_tiles_per_cu[0] << ", "
-          << t.many_tiles_per_cu[1] << "],\n  \"tile\": {\n";
+          << t.many_tiles_per_cu[1] << "],\n  \"small_by_time\": " << (t.small_by_time ? 1 : 0)
+          << ",\n  \"tile\": {\n";
         for (int m = 0; m < SPARKCL_TUNE_MODES; ++m) {
             o << "   \"" << kModeNames[m] << "\": {\n";
             for (int k = 0; k < 3; ++k) {
@@ -415,8 +418,8 @@ std::string tuning_to_json(const std::map<std::string, sparkcl_tuning> &all)
     return o.str();
 }
 
-bool tuning_load_file(const std::string &path, const std::string &arch,
-                      sparkcl_tuning *out, std::string *err)
+bool tuning_load_file(const std::string &path, const std::string &arch, TunedTable *out,
+                      std::string *err)
 {
     std::ifstream f(path);
     if (!f) {
@@ -426,7 +429,7 @@ bool tuning_load_file(const std::string &path, const std::string &arch,
     }
     std::stringstream ss;
     ss << f.rdbuf();
-    std::map<std::string, sparkcl_tuning> all;
+    std::map<std::string, TunedTable> all;
     if (!tuning_parse_json(ss.str(), &all, err))
         return false;
     auto it = all.find(arch);
@@ -439,10 +442,10 @@ bool tuning_load_file(const std::string &path, const std::string &arch,
     return true;
 }
 
-bool tuning_save_file(const std::string &path, const std::string &arch,
-                      const sparkcl_tuning &t, std::string *err)
+bool tuning_save_file(const std::string &path, const std::string &arch, const TunedTable &t,
+                      std::string *err)
 {
-    std::map<std::string, sparkcl_tuning> all;
+    std::map<std::string, TunedTable> all;
     {
         std::ifstream f(path);
         if (f) {

@@ -18,17 +18,18 @@ def cut():
     lib = ctypes.CDLL(libbuild.HOST_LIB)
     U32 = ctypes.c_uint32
     lib.hl_tuning_defaults.argtypes, lib.hl_tuning_defaults.restype = [ctypes.POINTER(sc.Tuning)], None
-    lib.hl_cut.argtypes = [ctypes.POINTER(sc.Tuning), U32, U32, ctypes.c_int,
-                           ctypes.POINTER(sc.Task), U32, U32, ctypes.POINTER(U32)]
+    lib.hl_cut.argtypes = [ctypes.POINTER(sc.Tuning), ctypes.POINTER(sc.Tuning), U32, U32,
+                           ctypes.c_int, ctypes.POINTER(sc.Task), U32, U32, ctypes.POINTER(U32)]
     lib.hl_cut.restype = ctypes.c_int
     table = sc.Tuning()
     lib.hl_tuning_defaults(ctypes.byref(table))
 
-    def f(tasks, mode=sc.BATCHED, per_cu=0, tuning=table):
+    def f(tasks, mode=sc.BATCHED, per_cu=0, tuning=table, tuned=table):
         tile = (U32 * len(tasks))()
-        by_time = lib.hl_cut(ctypes.byref(tuning), CUS, OCC, mode, (sc.Task * len(tasks))(*tasks),
-                             len(tasks), per_cu, tile)
+        by_time = lib.hl_cut(ctypes.byref(tuning), tuned and ctypes.byref(tuned), CUS, OCC, mode,
+                             (sc.Task * len(tasks))(*tasks), len(tasks), per_cu, tile)
         return bool(by_time), list(tile)
+    f.lib, f.table = lib, table
     return f
 
 
@@ -48,3 +49,38 @@ def test_unknown_kernel_ids(cut, kid, n):
                 good = [task(other, 300007)] * 3
                 assert cut([task(kid, n)] + good, mode, per_cu) == \
                     (cut(good, mode, per_cu)[0], [0] + cut(good, mode, per_cu)[1]), (mode, per_cu)
+
+
+def copy_of(t):
+    return sc.Tuning.from_buffer_copy(bytes(t))
+
+
+def test_callers_rows_are_the_cut(cut):
+    small = [task(sc.FMUL, 300_000)] * 4
+    assert cut(small)[0] and cut(small, tuning=copy_of(cut.table)) == cut(small)
+    own = copy_of(cut.table)
+    for mode in range(2):
+        own.tile[mode][1][18] = 1 << 13
+    assert cut(small, tuning=own) == (False, [1 << 13] * 4)
+    # the rows that a tuner left are tuned rows as well, any other table's not
+    assert cut(small, tuning=own, tuned=own)[0]
+    assert not cut(small, tuned=own)[0] and not cut(small, tuned=None)[0]
+    # rows that these calls do not read: batched, serving, Monte-Carlo
+    other = copy_of(cut.table)
+    other.tile[1][0][3] = other.tile[2][1][18] = other.tile[0][2][18] = 1 << 12
+    assert cut(small, tuning=other) == cut(small)
+    # enough work for the batched row, or Monte-Carlo tasks: the table
+    assert not cut([task(sc.FMUL, 1 << 24)] * 64)[0]
+    assert not cut(small + [sc.Task(kernel_id=sc.MC_PI, reduce_ops=sc.COUNT, n=1000)])[0]
+
+
+def test_cache_file_carries_the_rule(cut, tmp_path):
+    f = cut.lib.hl_tuning_small_by_time
+    f.argtypes = [ctypes.c_char_p, ctypes.c_char_p, ctypes.POINTER(sc.Tuning), ctypes.c_int]
+    f.restype = ctypes.c_int
+    path = str(tmp_path / "t.json").encode()
+    for arch, flag in ((b"a", 1), (b"b", 0), (b"a", 0), (b"b", 1)):
+        assert f(path, arch, ctypes.byref(cut.table), flag) == flag
+    # the library's own table is the autotuner's
+    text = open(sc.sparkcl.TUNING_PATH).read()
+    assert '"small_by_time": 1' in text
