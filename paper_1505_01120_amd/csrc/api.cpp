@@ -421,10 +421,9 @@ int sparkcl::build_plan(sparkcl_ctx *ctx, int kind, int mode, const sparkcl_task
         // map chains run 256-thread blocks; a given per_cu (chains) counts them
         p->block = kind == 4 ? (uint32_t)kBlock : exec_block(ctx, kid_mask);
         p->mc_only = mc_instance(ctx, kid_mask);
-        if (cut.per_cu)
-            per_cu = cut.per_cu;
-        p->grid = std::min(per_cu ? per_cu * (uint32_t)ctx->cus
-                                  : exec_grid(ctx, kid_mask, p->ntiles_total, ntasks, p->block),
+        p->grid = std::min(cut.grid ? cut.grid
+                           : per_cu ? per_cu * (uint32_t)ctx->cus
+                                    : exec_grid(ctx, kid_mask, p->ntiles_total, ntasks, p->block),
                            p->ntiles_total);
     }
     if (host_in) {

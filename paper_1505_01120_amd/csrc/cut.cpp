@@ -127,10 +127,10 @@ void even_cut(const ExecEnv *ctx, const sparkcl_task *tasks, uint32_t ntasks, ui
 {
     if (mask & (1u << (SPARKCL_MC_PI - 1)))
         return;
-    if (per_cu == 0)
-        per_cu = ctx->exec_blocks_per_cu ? ctx->exec_blocks_per_cu : 1;
-    const uint64_t grid = (uint64_t)per_cu * ctx->cus;
-    const double fixed = 110e3 / per_cu;
+    const uint64_t grid = per_cu                    ? (uint64_t)per_cu * ctx->cus
+                          : ctx->exec_blocks_per_cu ? exec_grid(ctx, mask)
+                                                    : ctx->cus;
+    const double fixed = 110e3 * ctx->cus / (double)grid;
     bool writes = false;
     uint64_t table_tiles = 0; // of the per-launch table
     for (uint32_t i = 0; i < ntasks; ++i) {
@@ -165,7 +165,7 @@ void even_cut(const ExecEnv *ctx, const sparkcl_task *tasks, uint32_t ntasks, ui
         }
     }
     if (c->even_bytes)
-        c->per_cu = per_cu;
+        c->grid = (uint32_t)grid;
 }
 
 } // namespace

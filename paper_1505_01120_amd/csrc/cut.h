@@ -18,10 +18,10 @@ struct Cut {
     // mixed batches: each kernel's tile derived from the batch's totals and
     // the tuned tiles per CU (index kernel id - 1; 0: none derived)
     uint32_t share_tile[3] = {0, 0, 0};
-    // small streaming batches: tiles of this many bytes, on per_cu executor
-    // blocks per CU (0: by the table)
+    // small streaming batches: tiles of this many bytes, on a grid of this many
+    // executor blocks (0: by the table)
     uint64_t even_bytes = 0;
-    uint32_t per_cu = 0;
+    uint32_t grid = 0;
 };
 
 // A batched call is "mixed" (takes sparkcl_tuning.tile_many) with at least

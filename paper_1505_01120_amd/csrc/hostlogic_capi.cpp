@@ -51,14 +51,17 @@ int hl_tasks_independent(const sparkcl_task *tasks, uint32_t ntasks)
 }
 
 // The cut of a call on a device of `cus` CUs that fit `occ` executor blocks
-// each, under table t with the rows of `tuned` (NULL: none) as tuned rows: 1 if
-// it is cut by estimated time, else 0; each task's tile size in tile[] (0 for
-// an unknown kernel id).
-int hl_cut(const sparkcl_tuning *t, const sparkcl_tuning *tuned, uint32_t cus, uint32_t occ,
-           int mode, const sparkcl_task *tasks, uint32_t ntasks, uint32_t per_cu, uint32_t *tile)
+// each and a caller that wants exec_blocks of them (0: as tuned), under table t
+// with the rows of `tuned` (NULL: none) as tuned rows: the grid if it is cut by
+// estimated time, else 0; each task's tile size in tile[] (0 for an unknown
+// kernel id).
+uint32_t hl_cut(const sparkcl_tuning *t, const sparkcl_tuning *tuned, uint32_t cus, uint32_t occ,
+                uint32_t exec_blocks, int mode, const sparkcl_task *tasks, uint32_t ntasks,
+                uint32_t per_cu, uint32_t *tile)
 {
     ExecEnv env;
     env.cus = (int)cus;
+    env.exec_blocks_per_cu = exec_blocks;
     env.occ_batch = env.occ_mc = (int)occ;
     if (tuned) {
         env.tuning = *tuned;
@@ -70,7 +73,7 @@ int hl_cut(const sparkcl_tuning *t, const sparkcl_tuning *tuned, uint32_t cus, u
         tile[i] = tasks[i].kernel_id >= SPARKCL_POLY && tasks[i].kernel_id <= SPARKCL_MC_PI
                       ? cut_tile(&env, c, tasks[i])
                       : 0;
-    return c.even_bytes != 0;
+    return c.grid;
 }
 
 // The passes of an array reduce as {count, chunk, rows, cpt, threads, groups,

@@ -140,9 +140,8 @@ extern "C" int sparkcl_reduce_noalloc(sparkcl_ctx *ctx, const sparkcl_task *task
             return fail(SPARKCL_ETOOBIG, "allocation-free reduce takes at most " +
                                              std::to_string(kMaxTiles) + " tiles, the call needs " +
                                              std::to_string(total_tiles));
-        grid = std::min<uint64_t>(cut.per_cu ? cut.per_cu * (uint32_t)ctx->cus
-                                             : exec_grid(ctx, kid_mask, total_tiles, ntasks),
-                                  total_tiles);
+        grid = std::min<uint64_t>(
+            cut.grid ? cut.grid : exec_grid(ctx, kid_mask, total_tiles, ntasks), total_tiles);
         block = exec_block(ctx, kid_mask);
 
         Partial *parts = reinterpret_cast<Partial *>(base + kOffParts);

@@ -18,17 +18,18 @@ def cut():
     lib = ctypes.CDLL(libbuild.HOST_LIB)
     U32 = ctypes.c_uint32
     lib.hl_tuning_defaults.argtypes, lib.hl_tuning_defaults.restype = [ctypes.POINTER(sc.Tuning)], None
-    lib.hl_cut.argtypes = [ctypes.POINTER(sc.Tuning), ctypes.POINTER(sc.Tuning), U32, U32,
+    lib.hl_cut.argtypes = [ctypes.POINTER(sc.Tuning), ctypes.POINTER(sc.Tuning), U32, U32, U32,
                            ctypes.c_int, ctypes.POINTER(sc.Task), U32, U32, ctypes.POINTER(U32)]
-    lib.hl_cut.restype = ctypes.c_int
+    lib.hl_cut.restype = U32
     table = sc.Tuning()
     lib.hl_tuning_defaults(ctypes.byref(table))
 
-    def f(tasks, mode=sc.BATCHED, per_cu=0, tuning=table, tuned=table):
+    def f(tasks, mode=sc.BATCHED, per_cu=0, tuning=table, tuned=table, exec_blocks=0):
         tile = (U32 * len(tasks))()
-        by_time = lib.hl_cut(ctypes.byref(tuning), tuned and ctypes.byref(tuned), CUS, OCC, mode,
-                             (sc.Task * len(tasks))(*tasks), len(tasks), per_cu, tile)
-        return bool(by_time), list(tile)
+        grid = lib.hl_cut(ctypes.byref(tuning), tuned and ctypes.byref(tuned), CUS, OCC,
+                          exec_blocks, mode, (sc.Task * len(tasks))(*tasks), len(tasks), per_cu,
+                          tile)
+        return grid, list(tile)
     f.lib, f.table = lib, table
     return f
 
@@ -61,7 +62,7 @@ def test_callers_rows_are_the_cut(cut):
     own = copy_of(cut.table)
     for mode in range(2):
         own.tile[mode][1][18] = 1 << 13
-    assert cut(small, tuning=own) == (False, [1 << 13] * 4)
+    assert cut(small, tuning=own) == (0, [1 << 13] * 4)
     # the rows that a tuner left are tuned rows as well, any other table's not
     assert cut(small, tuning=own, tuned=own)[0]
     assert not cut(small, tuned=own)[0] and not cut(small, tuned=None)[0]
@@ -84,3 +85,17 @@ def test_cache_file_carries_the_rule(cut, tmp_path):
     # the library's own table is the autotuner's
     text = open(sc.sparkcl.TUNING_PATH).read()
     assert '"small_by_time": 1' in text
+
+
+@pytest.mark.parametrize("block", [0, 256, 512, 1024])
+@pytest.mark.parametrize("exec_blocks", [1, 2, 3, OCC, OCC + 1, 100])
+def test_grid_is_resident(cut, block, exec_blocks):
+    # the caller's blocks per CU count 256 threads and are clipped to what fits,
+    # as for batches that the table cuts
+    t = copy_of(cut.table)
+    t.block[0] = t.block[1] = t.block_many = block
+    for tasks in ([task(sc.FMUL, 300_000)] * 4, [task(sc.POLY, 5000), task(sc.FMUL, 5000)]):
+        grid, _ = cut(tasks, tuning=t, exec_blocks=exec_blocks)
+        assert grid == max(1, min(exec_blocks, OCC) * 256 // (block or 256)) * CUS
+        assert cut(tasks, tuning=t)[0] == CUS
+        assert cut(tasks, tuning=t, per_cu=3)[0] == 3 * CUS

@@ -62,3 +62,26 @@ def test_autotuned(tasks, tmp_path):
     with sc.Context(device=0, arena_bytes=64 << 20, tune_cache=path) as ctx:
         loaded = cut(ctx, tasks)
     assert loaded == tuned
+
+
+@pytest.mark.parametrize("block", [256, 1024])
+def test_callers_blocks_per_cu(block):
+    # a small batch runs on no more blocks than a large one, which the table cuts
+    x = torch.rand(1 << 26, device="cuda")
+    large = [sc.task(sc.POLY, 1 << 20, x[i << 20:], coef=(1.0, 2.0)) for i in range(64)]
+    small = [sc.task(sc.POLY, 1 << 20, x[i << 20:], coef=(1.0, 2.0)) for i in range(3)]
+    with sc.Context(device=0, arena_bytes=64 << 20, exec_blocks_per_cu=100) as ctx:
+        t = ctx.get_tuning()
+        t.block[0] = block
+        for b in range(sc.TUNE_BUCKETS):
+            t.tile[1][0][b] = 1 << 13  # batched
+        ctx.set_tuning(t)
+        ctx.reduce(large, sc.BATCHED)
+        most = ctx.last_launch_shape()
+        assert most["tile_table"] == 1 and most["ntiles"] > most["grid"]
+        want, _ = ctx.reduce(small, sc.PER_LAUNCH)
+        got, _ = ctx.reduce(small, sc.BATCHED)
+        shape = ctx.last_launch_shape()
+        assert shape["tile_table"] == 0 and shape["grid"] <= most["grid"]
+        for g, w in zip(got, want):
+            assert abs(g.sum - w.sum) <= 1e-9 * w.sum and g.max == w.max
