@@ -75,8 +75,10 @@ struct TaskSync {
 static_assert(sizeof(TaskSync) == 16, "TaskSync layout");
 
 // Tasks of a blocking call whose results the launch itself writes to the host;
-// larger calls copy them.
-constexpr uint32_t kHostResults = 1024;
+// larger calls copy them.  One block writes them: of 300 FMUL tasks of 100
+// elements a call took 39.9 us with the copy and 37.1 without, of 400 43.3 and
+// 44.2, of 1024 76 and 86.
+constexpr uint32_t kHostResults = 384;
 
 // Persistent-executor queue state; every field returns to zero at kernel end
 // so the next launch needs no clearing.
