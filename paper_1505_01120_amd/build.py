@@ -74,9 +74,9 @@ def _run(cmd: list[str]) -> None:
 
 
 def isa_report(asm: str) -> dict:
-    """Per-kernel resources from the AMDGPU metadata, and the VALU count of
-    the Philox loop (the basic block of k_batch holding the most three-way
-    xors) from the device assembly text."""
+    """Per-kernel resources from the AMDGPU metadata, and the instructions of
+    the Philox loops of mixed batches (k_batch) and of Monte-Carlo ones
+    (k_batch_mc) from the device assembly text."""
     out = {}
     entries = asm[asm.find("amdhsa.kernels:"):].split("\n  - ")
     for k in KERNELS:
@@ -95,34 +95,35 @@ def isa_report(asm: str) -> dict:
                   "private_segment_bytes": field("private_segment_fixed_size"),
                   "vgpr_spills": field("vgpr_spill_count"),
                   "sgpr_spills": field("sgpr_spill_count")}
-    body = re.search(r"^_ZN7sparkcl12_GLOBAL__N_17k_batch\S*:(.*?)\.end_amdhsa_kernel",
-                     asm, re.S | re.M)
-    if body:
-        best, cur, cur_xor, best_xor = None, [], 0, 0
-        for line in body.group(1).splitlines() + [".LBB_end:"]:
-            t = line.strip()
-            if re.match(r"^\.LBB\d+_\d+:", t) or t.startswith("; %bb."):
-                if cur_xor > best_xor:
-                    best, best_xor = cur, cur_xor
-                cur, cur_xor = [], 0
-                continue
-            if not t or t.startswith(";") or t.startswith("."):
-                continue
-            op = t.split()[0]
-            cur.append(op)
-            if op == "v_bitop3_b32":
-                cur_xor += 1
-        if best:
-            out["philox_loop"] = {"valu": sum(1 for o in best if o.startswith("v_")),
-                                  "xor3": best_xor,
-                                  "mad_u64_u32": best.count("v_mad_u64_u32")}
+    out["philox_loop"] = philox_loop(asm, "_ZN7sparkcl12_GLOBAL__N_17k_batchE", 1)
+    with open(os.path.join(CSRC, "philox_dev.h")) as f:
+        pairs = int(re.search(r"constexpr int kMcPairs = (\d+);", f.read()).group(1))
+    out["mc_loop"] = philox_loop(asm, "_ZN7sparkcl12_GLOBAL__N_110k_batch_mcE", pairs)
     return out
+
+
+def philox_loop(asm: str, kernel: str, blocks: int) -> dict:
+    """The loop that draws a kernel's samples, `blocks` Philox blocks per
+    iteration: of its basic blocks the one with the most three-way xors."""
+    body = re.search("^" + kernel + r"\S*:(.*?)\.end_amdhsa_kernel", asm, re.S | re.M).group(1)
+    best, cur = [], []
+    for line in body.splitlines() + ["; %bb.end"]:
+        t = line.strip()
+        if re.match(r"^\.LBB\d+_\d+:", t) or t.startswith("; %bb."):
+            if cur.count("v_bitop3_b32") > best.count("v_bitop3_b32"):
+                best = cur
+            cur = []
+        elif t and t[0] not in ";.":
+            cur.append(t.split()[0])
+    return {"valu": sum(o.startswith("v_") for o in best), "blocks": blocks,
+            "xor3": best.count("v_bitop3_b32"), "mad_u64_u32": best.count("v_mad_u64_u32")}
 
 
 def probe_isa_report(asm: str) -> dict:
     """VALU instructions per loop iteration of each k_valu<mix> probe kernel:
     the v_ instructions of the kernel's loop block (the basic block that
-    branches back to its own label)."""
+    branches back to its own label; of the Monte-Carlo-only executor's loop,
+    which leaves it for points near the arc, the one with its Philox rounds)."""
     out = {}
     for m in re.finditer(r"^(_ZN12_GLOBAL__N_16k_valuILj(\d+)EEEv\S*):(.*?)\.end_amdhsa_kernel",
                          asm, re.S | re.M):
@@ -140,6 +141,7 @@ def probe_isa_report(asm: str) -> dict:
             cur.append(op)
             if op.startswith("s_cbranch") and label and t.split()[-1] == label:
                 out[mix] = sum(1 for o in cur if o.startswith("v_"))
+    out["1"] = philox_loop(asm, "_ZN12_GLOBAL__N_16k_valuILj1EEE", 2)["valu"]
     return {"valu_per_iteration": out}
 
 

@@ -407,14 +407,12 @@ __device__ __forceinline__ void tile_mc(uint64_t seed, uint32_t pid,
 // The same tile for the Monte-Carlo-only executor, which is bound by VALU
 // issue: the counter's high word is the same for a whole tile (tiles are
 // powers of two, at most 2^22 samples, and start at multiples of their
-// size), so the rounds it makes uniform run once per tile; the wave counts its misses in
-// scalar registers; kMcPairs independent blocks per iteration keep the
-// multiplies' latency covered at the executor's waves per SIMD.  (Mixed batches keep the body
+// size), so the rounds it makes uniform run once per tile, and the wave counts
+// its misses in scalar registers (wave_misses).  (Mixed batches keep the body
 // above: there the loop runs beside streaming tiles, which bound the time.)
 // Measured on MI355X, 256 partitions of 2^24 samples: 2440 us, 43 vector
 // instructions per pair of samples at 0.99 per CU and clock, against 2975 us
 // and 57 with the body above (2600 us and 47 with the words masked first).
-constexpr int kMcPairs = 2;
 __device__ __forceinline__ void tile_mc_uniform(uint64_t seed, uint32_t pid, uint64_t begin,
                                                 uint64_t end, Acc &a)
 {
@@ -427,25 +425,7 @@ __device__ __forceinline__ void tile_mc_uniform(uint64_t seed, uint32_t pid, uin
     uint32_t lo = (uint32_t)p0 + threadIdx.x;
     uint32_t misses = 0;
     for (uint32_t it = 0; it < iters; ++it) {
-        U4 r[kMcPairs];
-#pragma unroll
-        for (int u = 0; u < kMcPairs; ++u)
-            r[u] = ph.block(lo + u * B);
-        uint32_t now = 0, low = ~0u, h0, h1;
-#pragma unroll
-        for (int u = 0; u < kMcPairs; ++u) {
-            now += (uint32_t)__popcll(disc_miss_mask<true>(r[u].x, r[u].y, h0)) +
-                   (uint32_t)__popcll(disc_miss_mask<true>(r[u].z, r[u].w, h1));
-            low = min(low, min(h0, h1));
-        }
-        if (__ballot(low < kDiscBand) != 0) { // a point near the arc: all again, exactly
-            now = 0;
-#pragma unroll
-            for (int u = 0; u < kMcPairs; ++u)
-                now += (uint32_t)__popcll(disc_miss_mask<false>(r[u].x, r[u].y, h0)) +
-                       (uint32_t)__popcll(disc_miss_mask<false>(r[u].z, r[u].w, h1));
-        }
-        misses += now;
+        misses += wave_misses(ph, lo, B);
         lo += kMcPairs * B;
     }
     if ((threadIdx.x & 63u) == 0)

@@ -118,4 +118,33 @@ struct PhiloxTile {
     }
 };
 
+// One iteration of the Monte-Carlo-only executor's loop, and of the probe that
+// measures its ceiling: the samples outside the quarter disc among the pairs of
+// kMcPairs blocks per lane, at lo, lo + step, ..., counted for the whole wave,
+// all lanes active.  Independent blocks keep the multiplies' latency covered
+// at the executor's waves per SIMD.
+constexpr int kMcPairs = 2;
+__device__ __forceinline__ uint32_t wave_misses(const PhiloxTile &ph, uint32_t lo, uint32_t step)
+{
+    U4 r[kMcPairs];
+#pragma unroll
+    for (int u = 0; u < kMcPairs; ++u)
+        r[u] = ph.block(lo + u * step);
+    uint32_t misses = 0, low = ~0u, h0, h1;
+#pragma unroll
+    for (int u = 0; u < kMcPairs; ++u) {
+        misses += (uint32_t)__popcll(disc_miss_mask<true>(r[u].x, r[u].y, h0)) +
+                  (uint32_t)__popcll(disc_miss_mask<true>(r[u].z, r[u].w, h1));
+        low = min(low, min(h0, h1));
+    }
+    if (__ballot(low < kDiscBand) != 0) { // a point near the arc: all again, exactly
+        misses = 0;
+#pragma unroll
+        for (int u = 0; u < kMcPairs; ++u)
+            misses += (uint32_t)__popcll(disc_miss_mask<false>(r[u].x, r[u].y, h0)) +
+                      (uint32_t)__popcll(disc_miss_mask<false>(r[u].z, r[u].w, h1));
+    }
+    return misses;
+}
+
 } // namespace sparkcl

@@ -70,8 +70,8 @@ __global__ __launch_bounds__(kThreads) void k_read_ceiling(const float *x, const
 
 // ---- VALU ceiling ----------------------------------------------------------
 enum ValuMix : uint32_t {
-    MIX_PHILOX = 0,  // the Monte-Carlo loop body: one Philox block, two samples
-    MIX_PHILOX2 = 1, // two independent Philox blocks per iteration
+    MIX_PHILOX = 0,  // mixed batches' Monte-Carlo loop: one Philox block, two samples
+    MIX_PHILOX2 = 1, // the Monte-Carlo-only executor's: two blocks per iteration
     MIX_XOR3 = 2,    // v_bitop3_b32 three-way xors, 8 independent chains
     MIX_MAD64 = 3,   // v_mad_u64_u32 32x32+64 -> 64, 8 independent chains
     MIX_ADD = 4,     // v_add_u32, 8 independent chains
@@ -99,7 +99,17 @@ __global__ __launch_bounds__(kThreads) void k_valu(uint64_t seed, uint32_t pid, 
     const uint32_t gid = blockIdx.x * kThreads + threadIdx.x;
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
     uint32_t out = 0;
-    if constexpr (MIX == MIX_PHILOX || MIX == MIX_PHILOX2) {
+    if constexpr (MIX == MIX_PHILOX2) {
+        static_assert(sparkcl::kMcPairs == 2, "iterations of two blocks");
+        const uint32_t stride = gridDim.x * blockDim.x;
+        const sparkcl::PhiloxTile ph(0, pid, k0, k1);
+        uint32_t lo = gid, misses = 0;
+        for (uint32_t i = 0; i < iters; ++i) {
+            misses += sparkcl::wave_misses(ph, lo, stride);
+            lo += 2 * stride;
+        }
+        out = (threadIdx.x & 63u) == 0 ? 64u * 2u * 2u * iters - misses : 0u;
+    } else if constexpr (MIX == MIX_PHILOX) {
         // pair index p = gid + i * stride, as the tiles' threads stride over
         // their pairs
         const uint64_t stride = (uint64_t)gridDim.x * kThreads;
@@ -109,12 +119,6 @@ __global__ __launch_bounds__(kThreads) void k_valu(uint64_t seed, uint32_t pid, 
             const sparkcl::U4 r =
                 sparkcl::philox10(sparkcl::U4{(uint32_t)p, (uint32_t)(p >> 32), pid, 0u}, k0, k1);
             hits += sparkcl::disc_hit(r.x, r.y) + sparkcl::disc_hit(r.z, r.w);
-            if constexpr (MIX == MIX_PHILOX2) {
-                const uint64_t q = p + (uint64_t)iters * stride;
-                const sparkcl::U4 t = sparkcl::philox10(
-                    sparkcl::U4{(uint32_t)q, (uint32_t)(q >> 32), pid, 0u}, k0, k1);
-                hits += sparkcl::disc_hit(t.x, t.y) + sparkcl::disc_hit(t.z, t.w);
-            }
             p += stride;
         }
         out = hits;
@@ -191,16 +195,18 @@ extern "C" __attribute__((visibility("default"))) int
 sparkcl_probe_valu(uint32_t mix, uint32_t grid, uint32_t iters, uint64_t seed, uint32_t pid,
                    uint32_t *sink, uint64_t *clk, void *stream)
 {
-    // One launch of the VALU probe `mix` (0 Philox loop, 1 two Philox blocks
-    // per iteration, 2 xor3, 3 mad_u64_u32, 4 add_u32, 5 mul_hi_u32, 6 xor3
+    // One launch of the VALU probe `mix` (0 mixed batches' Philox loop,
+    // 1 the Monte-Carlo-only one, 2 xor3, 3 mad_u64_u32, 4 add_u32, 5 mul_hi_u32, 6 xor3
     // and add_u32, 7 mad_u64_u32 and add_u32) with
     // `grid` blocks of 256 threads, `iters` iterations per thread, on
     // `stream`.  sink: grid * 256 words (device); clk: 4 words (device),
     // receiving block 0's (shader clock, wall clock) at its start and its end.
     // A Philox probe covers pairs [0, grid * 256 * iters) (twice that for
-    // mix 1) of partition `pid` under key `seed`, the same pairs a
-    // Monte-Carlo partition of that many samples draws.  SPARKCL_EINVAL for
-    // a bad argument, nothing launched.
+    // mix 1, whose pairs have to be at most 2^32) of partition `pid` under key
+    // `seed`, the same pairs a Monte-Carlo partition of that many samples
+    // draws.  SPARKCL_EINVAL for a bad argument, nothing launched.
+    if (mix == MIX_PHILOX2 && 2ull * kThreads * grid * iters > 1ull << 32)
+        return SPARKCL_EINVAL;
     if (!sink || !clk || grid == 0 || grid > 65535u * 16u || iters == 0 || mix >= MIX_COUNT)
         return SPARKCL_EINVAL;
     if ((uintptr_t)sink & 3u || (uintptr_t)clk & 7u)
