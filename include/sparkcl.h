@@ -472,8 +472,9 @@ SPARKCL_API int sparkcl_wordcount(sparkcl_ctx *ctx, const uint8_t *text, uint64_
    key it is, written to offsets[] (device, nkeys entries, caller-owned);
    UINT64_MAX for a key that no word of the text has.  The word is the run
    of non-whitespace bytes starting there.  One pass over the text plus a
-   lookup table from the arena (12 B per slot, two slots per key, at least
-   1024): ENOMEM if it does not fit; EINVAL if a key appears twice (offsets
+   lookup table from the arena (16 B per slot, 1.5 to 3 slots per key, at
+   least 768; up to 2^15 slots it takes four times as many where those fit):
+   ENOMEM if it does not fit; EINVAL if a key appears twice (offsets
    are then unspecified); ETOOBIG if nkeys exceeds 2^32 - 1 or nbytes
    exceeds 2^40.  Blocking. */
 SPARKCL_API int sparkcl_wordcount_locate(sparkcl_ctx *ctx, const uint8_t *text,

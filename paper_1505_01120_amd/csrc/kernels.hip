@@ -1127,7 +1127,6 @@ __global__ __launch_bounds__(kBlock) void k_map(const TaskDev *__restrict__ task
     }
 }
 
-// Clears library workspaces with a kernel (no memset nodes in captured work).
 // ---- array-valued ReduceCL ----------------------------------------------------
 // The RDD's elements are float arrays of one length; the two-input combiner
 // (Fig 3 adds two arrays elementwise) folds them pairwise along a fixed
@@ -1477,8 +1476,9 @@ __global__ __launch_bounds__(BT) void k_tree_wide(TreeArgs a)
             TreeVec<4>::st(o + col[c], acc[c], skip[c]);
 }
 
-// (16 bytes per store from the first 16-byte boundary on: 16 MiB in 8.2 us, in
-// single words 9.2.)
+// Clears library workspaces with a kernel (no memset nodes in captured work),
+// 16 bytes per store from the first 16-byte boundary on: 16 MiB in 8.2 us, in
+// single words 9.2.
 __global__ __launch_bounds__(kBlock) void k_zero(uint32_t *p, uint64_t words)
 {
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
@@ -1506,13 +1506,15 @@ __global__ __launch_bounds__(kBlock) void k_zero(uint32_t *p, uint64_t words)
 // paper's "local data").  The table absorbs the frequent words of a skewed
 // vocabulary; a word that finds no place in its set is appended to the
 // block's spill region of its key's partition (a plain store at an
-// LDS-counted position); a merge kernel then counts each partition's spilled
-// keys in LDS and adds each distinct key once to the global open-addressing
+// LDS-counted position), and the table itself is written out whole at the end;
+// a merge kernel then counts each partition's keys, spilled and from the
+// tables, in LDS and adds each distinct key once to the global open-addressing
 // table.  (Adding every such word to the global table with a device-scope
 // atomic cost more than the scan: those atomics are carried out at the memory
-// side, one round trip each.)  The LDS tables themselves, and the words that
-// overflow a spill region, go to the table with atomics.  Counts are integers,
-// so the result does not depend on which block counts which word.
+// side, one round trip each.)  Words that overflow a spill region go to the
+// global table with atomics, and without spill regions every miss and every
+// block's table.  Counts are integers, so the result does not depend on which
+// block counts which word.
 //
 // Two blocks of 8 waves per CU with tables of 4096 keys: smaller ones hold the
 // same few frequent words several times over (four of 2048 keys), and one of 16
@@ -1581,9 +1583,6 @@ __device__ void wc_global_add(const WcArgs &a, uint64_t h, uint64_t c)
     atomicOr((unsigned long long *)&a.ctl[2], 1ull); // table full
 }
 
-// The LDS counts are 32-bit: a block counts at most one word per two bytes
-// of the text it scans, and a block scans either a few KiB or about 1/512 of
-// the text (a grid of two blocks per CU), which is limited to 2^40 bytes.
 // A word that found no LDS slot: appended to this block's spill region of
 // its partition, or, when the region is full (or there are none, or its key
 // is 0), added to the table directly.  scnt: the block's per-partition
@@ -2015,6 +2014,9 @@ __device__ __forceinline__ uint64_t wc_scan(const uint8_t *text, uint64_t n, uin
 __global__ __launch_bounds__(kWcScanBlock, 4) void k_wordcount(WcArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint64_t sk[kWcSlots];
+    // 32 bits each: a block counts at most one word per two bytes of the text it
+    // scans, and it scans either a few KiB or about 1/512 of the text (a grid of
+    // two blocks per CU), which is limited to 2^40 bytes
     __shared__ uint32_t sc[kWcSlots];
     __shared__ uint32_t scnt[1u << kWcPartBits];    // spill appends per partition
     const uint32_t tid = threadIdx.x;
@@ -2316,7 +2318,7 @@ __global__ __launch_bounds__(kWcBlock) void k_wc_merge(WcArgs a, uint32_t scan_g
             wc_global_add(a, h, c);
             return;
         }
-        // 32 bits hold a block's words (above); a partition's, of all blocks,
+        // 32 bits hold a block's words (k_wordcount); a partition's, of all blocks,
         // may pass them: what carries goes to the table
         const uint32_t old = atomicAdd(&mc[s], c);
         if (old + c < old)
