@@ -1538,8 +1538,8 @@ constexpr uint32_t kWcCompact = 4 * kWcBlock; // table slots of a compaction blo
 constexpr uint32_t kWcMissed = 2 * 64;     // those that found no place in the table
 constexpr uint32_t kWcPartSets = kWcSets >> kWcPartBits;
 // Locating keeps offsets beside the words, so its table is smaller.
-constexpr uint32_t kWlSets = 1536;
-constexpr uint32_t kWlFew = 2048;
+constexpr uint32_t kWlSets = 1760;
+constexpr uint32_t kWlFew = 512;
 
 __device__ __forceinline__ bool wc_space(uint32_t b)
 {
@@ -2154,11 +2154,13 @@ __device__ __forceinline__ void wl_lookup(const WlArgs &l, uint64_t h, uint64_t 
 }
 
 // FEW: at most kWlFew keys are wanted, and most words are none of them.  A bit
-// for each of 16384 values of a word's hash then drops those first, which
+// for each of 4096 values of a word's hash then drops those first, which
 // otherwise pass through the block's table, the second queue and the global
 // table, and the block that ends last writes the results, which saves a launch.
 // Ten keys in 128 MiB of 8-letter words that hardly repeat: 191 us without the
 // bits, 146 so; in 256 MiB of Zipf text 308 and 244, in 4 KiB 32 and 31 a call.
+// (Where every word is wanted the bits only cost: 1000 keys in 128 MiB of just
+// these words 190 us without them, 198 with.)
 constexpr uint32_t kWlBits = 8 * kWlFew;
 __device__ __forceinline__ uint32_t wl_bit(uint64_t h)
 {

@@ -11,7 +11,7 @@ import paper_1505_01120_amd as sc
 
 pytestmark = pytest.mark.gpu
 
-FEW = 2048
+FEW = 512
 
 
 @pytest.fixture(scope="module")
