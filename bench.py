@@ -588,8 +588,8 @@ def bench_wordcount(ctx, sc, reps=5) -> dict:
             "locate": {"ms": loc_sec * 1e3, "GBps": nbytes / loc_sec / 1e9, "keys": nd,
                        "matches_oracle": loc_exact,
                        "what": "first byte offset of each distinct key's word"},
-            # the scan kernel issues about 0.29 VALU, 0.19 SALU and 0.025 LDS
-            # wave-instructions per text byte, the VALU 68% of its cycles: it
+            # the scan kernel issues about 0.30 VALU, 0.20 SALU and 0.026 LDS
+            # wave-instructions per text byte, the VALU 66% of its cycles: it
             # is bound by instruction issue, not by HBM (counters in the
             # WordCount profile summary)
             "bound": {"kind": "issue (VALU, SALU, LDS table inserts)",

@@ -1524,11 +1524,12 @@ __global__ __launch_bounds__(kBlock) void k_zero(uint32_t *p, uint64_t words)
 // registers leave room for one of 8 waves.
 //
 // Measured on MI355X, 512 MiB of Zipf text (10^5 words), whole call with its
-// sort of the keys: 1400-1575 us with one word per lane hashed byte by byte
-// from LDS and the tables added to the global one by atomics, 643 us so; 256
-// MiB of 2 10^5 words 4350 and 455 us.  Of the scan's 435 us its walk takes 320
-// without a word kept; places 55; the second queue and the tables written
-// out whole took 150 off what misses and atomics cost.
+// sort of the keys: 1440-1575 us with one word per lane hashed byte by byte
+// from LDS and the tables added to the global one by atomics, 634 us so; 128
+// MiB of 2 10^5 words, without the sort, 2155 and 250 us.  Of the scan's 435 us
+// (one block of 16 waves) its walk took 320 without a word kept; places 55; the
+// second queue and the tables written out whole took 150 off what misses and
+// atomics cost.
 constexpr int kWcScanBlock = (int)kWcWaves * 64;
 constexpr int kWcBlock = 1024; // of the merge and the compaction
 constexpr uint32_t kWcBlockWaves = kWcBlock / 64;
@@ -2078,7 +2079,7 @@ __global__ void k_wc_pad(const uint8_t *text, uint64_t n, uint8_t *out)
 // 64 of them, so that a wave reads the table for all its lanes: random reads
 // of L2, which bound the pass without the LDS keys (one in three words comes
 // to the table), and are one per word with key and offset side by side.  256 MiB
-// of Zipf text, 10^5 keys: 759 us with three reads for every word, 474 us now.
+// of Zipf text, 10^5 keys: 762 us with three reads for every word, 499 us now.
 // (the table's size is no power of two; Knuth's multiplicative hash of the key)
 __device__ __forceinline__ uint64_t wl_slot(uint64_t h, uint64_t slots)
 {

@@ -158,8 +158,8 @@ int sparkcl_wordcount_locate(sparkcl_ctx *ctx, const uint8_t *text, uint64_t nby
     // A block's LDS keys settle a word only once one before it has been met, so
     // the spans of a first chunk, which the waves walk side by side, gain
     // little by them: shorter ones while there would be fewer than four chunks
-    // (100 MiB: 246 us in two of 192 bytes, 226 in three of 128; 256 MiB: 463 in
-    // four of 256, 467 in eight of 128).
+    // (100 MiB: 270 us in two of 192 bytes, 252 in three of 128; 256 MiB: 482 in
+    // four of 256, 489 in eight of 128).
     const uint64_t lanes = 64ull * kWcWaves * kWcPerCu * (uint64_t)ctx->cus;
     scan_geometry(ctx, nbytes, nbytes < 4 * kWlMaxSpan * lanes ? kWlMaxSpan / 2 : kWlMaxSpan,
                   &span, &grid);
